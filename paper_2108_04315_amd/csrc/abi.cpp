@@ -277,6 +277,34 @@ static void band_weights(int N, int s, double t, int P, const double *psf, int L
     }
 }
 
+// Weights of an LR row that the image edge does not cut (the same sums as
+// band_weights, in its order), and the run [lo, hi) of rows, around the
+// middle one, that equal them at every tap inside the image.
+static void canonical_row(int N, int s, double t, int P, const double *psf, int Lp, int off,
+                          const float *rows, float *cw, int *lo, int *hi) {
+    const int R = (P - 1) / 2, n = N / s;
+    const double fl = std::floor(t), f = t - fl;
+    std::vector<double> acc((size_t)Lp, 0.0);
+    for (int b = 0; b < s; ++b)
+        for (int a = -R; a <= R; ++a)
+            for (int e = 0; e < 2; ++e) {
+                const double wgt = e ? f : 1.0 - f;
+                if (wgt != 0.0) acc[b - a + (int)fl + e - off] += psf[a + R] * wgt / s;
+            }
+    for (int l = 0; l < kMaxL; ++l) cw[l] = l < Lp ? (float)acc[l] : 0.f;
+    auto same = [&](int i) {
+        for (int l = 0; l < Lp; ++l) {
+            const int v = s * i + off + l;
+            if (v >= 0 && v < N && !(rows[(size_t)i * Lp + l] == cw[l])) return false;
+        }
+        return true;
+    };
+    *lo = *hi = n / 2;
+    while (*hi < n && same(*hi)) ++*hi;
+    while (*lo > 0 && *hi > n / 2 && same(*lo - 1)) --*lo;
+    if (*hi == *lo) *lo = *hi = 0;   // none: every row takes the table's
+}
+
 // ---------------------------------------------------- general operators
 // Row (k, i, j) of A = [A_0; ...; A_{K-1}] for an affine warp and a P x P PSF:
 // D averages the s x s block of HR samples (U, V) = (s i + a, s j + b); B
@@ -636,6 +664,12 @@ extern "C" misr_status misr_op_create(misr_ctx *ctx, const misr_geometry *g, mis
                      wy.data() + k * fy + (size_t)kPadRows * op->Lp);
         band_weights(op->W, op->s, tx, op->P, taps + op->P, op->Lp, hd.offx[k],
                      wx.data() + k * fx + (size_t)kPadRows * op->Lp);
+        canonical_row(op->H, op->s, ty, op->P, taps, op->Lp, hd.offy[k],
+                      wy.data() + k * fy + (size_t)kPadRows * op->Lp, hd.cwy[k], &hd.loy[k],
+                      &hd.hiy[k]);
+        canonical_row(op->W, op->s, tx, op->P, taps + op->P, op->Lp, hd.offx[k],
+                      wx.data() + k * fx + (size_t)kPadRows * op->Lp, hd.cwx[k], &hd.lox[k],
+                      &hd.hix[k]);
     }
     MISR_HIP(op->wy.ensure(wy.size() * 4));
     MISR_HIP(op->wx.ensure(wx.size() * 4));

@@ -61,6 +61,7 @@ FI unsigned pixel_hash(long long gidx, unsigned seed) {
 struct StF32 {
     using raw = float;
     static constexpr int code = ST_F32;
+    static FI float cv(raw v) { return v; }
     static FI float ld(const AS1 raw *p, i64 i) { return p[i]; }
     static FI float rnd(float v) { return v; }
     static FI float rnd_sr(float v, unsigned) { return v; }
@@ -69,6 +70,7 @@ struct StF32 {
 struct StF16 {
     using raw = _Float16;
     static constexpr int code = ST_F16;
+    static FI float cv(raw v) { return (float)v; }
     static FI float ld(const AS1 raw *p, i64 i) { return (float)p[i]; }
     static FI float rnd(float v) { return (float)(_Float16)v; }
     static FI float rnd_sr(float v, unsigned h) {
@@ -85,6 +87,7 @@ struct StF16 {
 struct StU16 {
     using raw = unsigned short;
     static constexpr int code = ST_U16;
+    static FI float cv(raw v) { return (float)v; }
     static FI float ld(const AS1 raw *p, i64 i) { return (float)p[i]; }
 };
 struct StBF16 {
@@ -96,7 +99,8 @@ struct StBF16 {
         u += 0x7fffu + ((u >> 16) & 1u);
         return (unsigned short)(u >> 16);
     }
-    static FI float ld(const AS1 raw *p, i64 i) { return __uint_as_float((unsigned)p[i] << 16); }
+    static FI float cv(raw v) { return __uint_as_float((unsigned)v << 16); }
+    static FI float ld(const AS1 raw *p, i64 i) { return cv(p[i]); }
     static FI float rnd(float v) { return __uint_as_float((unsigned)bits(v) << 16); }
     static FI float rnd_sr(float v, unsigned h) {
         unsigned u = __float_as_uint(v);

@@ -14,8 +14,17 @@
 // A_k = C_y,k (x) C_x,k holds exactly because the warp, the PSF and the
 // binning of the observation model (Sec. 3.1, Eq. sisr) are all separable,
 // zero padding included, so each 2-D operator becomes two 1-D banded ones.
-// Band weights are read per LR row/column from the operator's tables with
-// wave-uniform (scalar) loads: every pass maps one weight row to one wave.
+// Each wave runs whole strips of an operator (pass 1 and 2 of its own LR
+// columns, pass 3 and 4 of its own HR columns), so that its passes follow each
+// other in its own LDS without a workgroup barrier; only the residual crosses
+// waves (one barrier per frame).  The weights of all rows and columns away
+// from the image edge are the same L numbers per frame and axis: a frame's
+// 2 L weights sit in scalar registers.  What bounds the passes is the latency
+// of their chain (LDS round trips, barriers, scalar loads) and VALU issue: one
+// barrier instead of four per frame and no per-row weight loads took the
+// standalone adjoint of 9 frames of 1024^2 at x3 from 157 to 98 us, k_trial
+// from 64.6 to 56.5 us at 2048^2 x2 (4 frames) and from 779 to 537 us at
+// 6144^2 x3 (9 frames).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -37,13 +46,31 @@ constexpr int kNWI = kNTI / 64;    // waves per workgroup
 // variant 2 is a trial-kernel shape as wide as the trial pass's LDS alone
 // allows (the update pass stages two windows), paired with variant 0's
 // update shape.
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+constexpr int odd(int v) { return (v % 2) ? v : v + 1; }
+
+// A wave's strip of a forward over NI x NJ LR pixels: pass 1 gives every
+// wave CJ neighbouring LR columns (lanes on HR rows), pass 2 lays the strip's
+// CI-row blocks x CJ columns over the lanes.
+template <int S, int L, int NI, int NJ>
+struct Strip {
+    static constexpr int CJ = ceil_div(NJ, kNWI);
+    static constexpr int calc_ci() {
+        int ci = 1;
+        while (ceil_div(NI, ci) * CJ > 64) ++ci;
+        return ci;
+    }
+    static constexpr int CI = calc_ci();
+    static constexpr int NIB = ceil_div(NI, CI);
+    static constexpr int HS = 65;   // column stride of the wave's pass-1 output
+    static constexpr int rows = S * (NIB * CI - 1) + L;
+    static constexpr int LDS = (CJ - 1) * HS + (rows > 64 ? rows : 64);
+};
+
 template <int S, int L, int TV>
 struct Tile {
     static constexpr int EXT = (L - 1 > 2) ? L - 1 : 2;   // window margin (HR px)
     static constexpr int NTAP = (L + S - 1) / S;         // adjoint taps per output
-    static constexpr int CJ = 4;                         // pass 1 LR columns per wave step
-    static constexpr int CI = 4;                         // pass 2 LR rows per wave step
-    static constexpr int CU = (S == 4) ? 8 : 6;          // pass 3 HR rows per wave step
     static constexpr int calc_th() {
         int best = S;
         for (int th = S; th + 2 <= 64; th += S)
@@ -53,24 +80,24 @@ struct Tile {
     static constexpr int TH = calc_th();
     static constexpr int NIM = (TH + L - 2) / S + 1;     // LR rows touching the tile
     static constexpr int NRM = S * (NIM - 1) + L;        // HR rows those read
-    static constexpr int odd(int v) { return (v % 2) ? v : v + 1; }
-    // LDS floats of a tile tw wide: the trial pass's, and the update pass's
-    // unless the shape is the trial kernel's own (variant 2)
-    static constexpr int lds_floats(int tw) {
+    // LDS floats by which the tile's width is chosen: a window, one LR row
+    // set in pass-1 and residual form, and the owned p (trial pass), or two
+    // windows (update pass, unless the shape is the trial kernel's own)
+    static constexpr int shape_floats(int tw) {
         const int wcp = odd(tw + 2 * EXT);
         const int njp = odd((tw + L - 2) / S + 1);
-        const int xs = (TH + 2 * EXT) * wcp + S * CJ + 8;
-        const int hx = NRM * njp + S * CI * njp;
+        const int xs = (TH + 2 * EXT) * wcp + S * 4 + 8;
+        const int hx = NRM * njp + S * 4 * njp;
         const int hr = hx + NIM * njp;
         const int gs = TH * (tw + 1);
-        const int trial = xs + (hr > gs ? hr : gs) + TH * tw;   // + the owned p
-        const int upd = 2 * xs + hx + NIM * njp;                // + A_k x for p = 1
+        const int trial = xs + (hr > gs ? hr : gs) + TH * tw;
+        const int upd = 2 * xs + hx + NIM * njp;
         return (TV == 2 || trial > upd) ? trial : upd;
     }
     static constexpr int calc_tw() {
         int best = kNWI * S;
         for (int tw = kNWI * S; tw <= 1024; tw += kNWI * S)
-            if ((tw + L - 2) / S + 1 <= 64 && lds_floats(tw) * 4 <= 79 * 1024) best = tw;
+            if ((tw + L - 2) / S + 1 <= 64 && shape_floats(tw) * 4 <= 79 * 1024) best = tw;
         // variant 1: about half as wide (more workgroups for small images)
         if (TV == 1) {
             const int half = best / 2 / (kNWI * S) * (kNWI * S);
@@ -80,186 +107,260 @@ struct Tile {
     }
     static constexpr int TW = calc_tw();
     static constexpr int WR = TH + 2 * EXT, WC = TW + 2 * EXT, WCP = odd(WC);
-    static constexpr int NJM = (TW + L - 2) / S + 1;
-    static constexpr int NJP = odd(NJM);
+    static constexpr int NJM = (TW + L - 2) / S + 1;     // LR columns touching the tile
     static constexpr int CV = TW / kNWI;                 // pass 4 / prior columns per wave
-    static constexpr int XS = WR * WCP + S * CJ + 8;
-    static constexpr int HXS = NRM * NJP + S * CI * NJP;
-    static constexpr int RSS = NIM * NJP;
+    using FT = Strip<S, L, NIM, NJM>;                    // the trial's forward
+    using FU = Strip<S, L, TH / S, TW / S>;              // forward of the owned LR pixels
+    // adjoint strip: the CV columns of a wave gather from at most NJG LR
+    // columns; pass 3 lays those x NUB blocks of CU rows over the lanes
+    static constexpr int NJG = (S - 1 + CV - 1) / S + NTAP;
+    static constexpr int CU = ceil_div(ceil_div(TH, 64 / NJG), S) * S;
+    static constexpr int NUB = ceil_div(TH, CU);
+    static constexpr int TS = odd(NUB * CU);             // column stride of pass 3's output
+    static constexpr int XS = WR * WCP + S * kNWI * FT::CJ + 8;
+    static constexpr int PWT = FT::LDS > NJG * TS ? FT::LDS : NJG * TS;   // per wave, trial
+    static constexpr int RP = kNWI * FT::CJ + 1;         // row stride of the residual
+    static constexpr int RSR = FT::NIB * FT::CI > NIM ? FT::NIB * FT::CI : NIM;
+    static constexpr int RSS = RSR * RP;                 // one residual buffer of two
+    static constexpr int RSX = ((NUB * CU - TH) / S + 2) * RP;   // rows the padded blocks read
     static constexpr int GP = TW + 1;                    // row stride of the LDS gradient
-    static constexpr int SMEM = lds_floats(TW);
-    static_assert(NRM <= 64 && TH + 2 <= 64 && NJM <= 64, "a wave spans a tile dimension");
+    static constexpr int BANDS = kNWI * PWT + 2 * RSS + RSX;
+    static constexpr int PO = XS + (BANDS > TH * GP ? BANDS : TH * GP);
+    // the owned p stays in LDS where two workgroups per CU still fit, else
+    // the output re-reads it
+    static constexpr bool POL = (PO + TH * TW) * 4 <= 79 * 1024;
+    static constexpr int SMEM = PO + (POL ? TH * TW : 0);
+    static constexpr int SMEM_U = 2 * XS + kNWI * FU::LDS;          // update pass
+    static constexpr int SMEM_F = XS + kNWI * FU::LDS;              // standalone forward
+    static constexpr int SMEM_A = XS + kNWI * PWT + 2 * RSS + RSX;  // standalone adjoint
+    static_assert(NRM <= 64 && TH + 2 <= 64 && NJM <= 64 && NJG <= 64, "a wave spans a dimension");
     static_assert(CV % S == 0 && CU % S == 0, "phase-aligned groups");
-    static constexpr int PO = XS + ((HXS + RSS > TH * GP) ? HXS + RSS : TH * GP);
-    static_assert(TH * GP <= SMEM - XS && TH <= NRM, "LDS aliasing");
-    static_assert(PO + TH * TW <= SMEM, "LDS: owned p of the trial pass");
+    static_assert(TH * GP <= XS, "the standalone adjoint's output tile");
+    static_assert(SMEM * 4 <= 81408 && (TV == 2 || SMEM_U * 4 <= 81408), "two workgroups per CU");
 };
 
-// pass 1: hx[r][j] = sum_l wx[jA+j][l] win[wr0+r][wc0+S j+l], r < NR, j < NJ.
-// Waves take groups of CJ LR columns (their weights are scalar loads), lanes
-// take rows; each lane keeps the S(CJ-1)+L window samples it needs in
-// registers.
-template <int S, int L, int TV>
-FI void pass1(const float *win, int wr0, int wc0, int NR, int NJ, const AS4 float *wxk, int jA,
-              int jlast, float *hx) {
-    using T = Tile<S, L, TV>;
-    constexpr int CJ = T::CJ, NX = S * (CJ - 1) + L;
-    const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-    for (int jg = wv; jg * CJ < NJ; jg += kNWI) {
-        const int j0 = jg * CJ;
-        // rows past the end of the table read its zero padding
-        const AS4 float *wb = wxk + (jA + j0) * L;
-        float wgt[CJ][L];
+// Orders a wave's LDS writes before its own lanes' later reads: DS operations
+// of one wave complete in order, so only the compiler has to keep them so.
+FI void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One frame's band weights along one axis.  Every LR row whose taps are not
+// cut by the image edge has the same L weights, c (scalar registers for a
+// whole frame); rows outside [lo, hi) (a few at either edge) take theirs from
+// the table, whose row -1 and row n are zero.
+template <int L>
+struct AxisW {
+    float c[L];
+    int lo, hi, n;
+    const AS4 float *tab;
+    // some LR row of [i, i + m) has weights of its own (uniform)
+    FI bool special(int i, int m) const {
+        return max(i, 0) < min(i + m, lo) || max(i, hi) < min(i + m, n);
+    }
+    FI const AS4 float *row(int i) const { return tab + min(max(i, -1), n) * L; }
+};
+template <int L>
+FI AxisW<L> axis_y(const AS4 OpDev &op, int k) {
+    AxisW<L> a;
 #pragma unroll
-        for (int c = 0; c < CJ; ++c)
+    for (int l = 0; l < L; ++l) a.c[l] = op.cwy[k][l];
+    a.lo = op.loy[k];
+    a.hi = op.hiy[k];
+    a.n = op.H / op.s;
+    a.tab = cst(op.wy) + (i64)k * op.fsy * L;
+    return a;
+}
+template <int L>
+FI AxisW<L> axis_x(const AS4 OpDev &op, int k) {
+    AxisW<L> a;
 #pragma unroll
-            for (int l = 0; l < L; ++l) wgt[c][l] = wb[c * L + l];
-        if (lane < NR) {
-            const float *src = win + (wr0 + lane) * T::WCP + wc0 + S * j0;
-            float xv[NX];
+    for (int l = 0; l < L; ++l) a.c[l] = op.cwx[k][l];
+    a.lo = op.lox[k];
+    a.hi = op.hix[k];
+    a.n = op.W / op.s;
+    a.tab = cst(op.wx) + (i64)k * op.fsx * L;
+    return a;
+}
+
+// A wave's strip of the forward: the NI LR rows from i0 at the CJ LR columns
+// from j0 + CJ wv.  win: the window at the first tap of LR pixel (i0, j0).
+//   pass 1 (lanes on HR rows): hx[c][r] = sum_l wx[j][l] win[r][S (CJ wv + c) + l]
+//   pass 2 (lanes on CI-row blocks x columns): sum_l wy[i][l] hx[c][S i + l]
+// Both passes of a strip belong to one wave, so nothing but that wave's own
+// LDS order separates them (no workgroup barrier), and every frame's weights
+// are the same scalars for all rows and columns away from the image edge.
+// out(i, c, v[CI]): the results of LR rows i.. of the strip's column c.
+template <int S, int L, class G, class F>
+FI void fwd_strip(const float *win, int wcp, float *hx, const AxisW<L> &ay, const AxisW<L> &ax,
+                  int i0, int j0, int lane, int wv, F out) {
+    constexpr int CJ = G::CJ, CI = G::CI, NX = S * (CJ - 1) + L, NH = S * (CI - 1) + L;
+    const int jw = j0 + CJ * wv;
+    {
+        const float *src = win + lane * wcp + S * CJ * wv;
+        float xv[NX];
 #pragma unroll
-            for (int t = 0; t < NX; ++t) xv[t] = src[t];
+        for (int t = 0; t < NX; ++t) xv[t] = src[t];
+        if (!ax.special(jw, CJ)) {
 #pragma unroll
             for (int c = 0; c < CJ; ++c) {
                 float a = 0.f;
 #pragma unroll
-                for (int l = 0; l < L; ++l) a = fmaf(wgt[c][l], xv[S * c + l], a);
-                if (j0 + c < NJ) hx[lane * T::NJP + j0 + c] = a;
+                for (int l = 0; l < L; ++l) a = fmaf(ax.c[l], xv[S * c + l], a);
+                hx[c * G::HS + lane] = a;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < CJ; ++c) {
+                const AS4 float *wb = ax.row(jw + c);
+                float a = 0.f;
+#pragma unroll
+                for (int l = 0; l < L; ++l) a = fmaf(wb[l], xv[S * c + l], a);
+                hx[c * G::HS + lane] = a;
             }
         }
     }
-}
-
-// pass 2: a = sum_l wy[iA+i][l] hx[S i + l][j]; waves take groups of CI LR
-// rows, lanes take LR columns; out(i, j, a) consumes each result.
-template <int S, int L, int TV, class F>
-FI void pass2(const float *hx, int NI, int NJ, const AS4 float *wyk, int iA, int ilast, F out) {
-    using T = Tile<S, L, TV>;
-    constexpr int CI = T::CI, NH = S * (CI - 1) + L;
-    const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-    for (int ig = wv; ig * CI < NI; ig += kNWI) {
-        const int i0 = ig * CI;
-        const AS4 float *wb = wyk + (iA + i0) * L;
-        float wgt[CI][L];
+    wave_lds_order();
+    const int ib = lane / CJ, cj = lane - ib * CJ;
+    if (ib < G::NIB) {
+        const float *src = hx + cj * G::HS + S * CI * ib;
+        float hv[NH], av[CI];
 #pragma unroll
-        for (int c = 0; c < CI; ++c)
-#pragma unroll
-            for (int l = 0; l < L; ++l) wgt[c][l] = wb[c * L + l];
-        if (lane < NJ) {
-            float hv[NH];
-#pragma unroll
-            for (int t = 0; t < NH; ++t) hv[t] = hx[(S * i0 + t) * T::NJP + lane];
-            float av[CI];
+        for (int t = 0; t < NH; ++t) hv[t] = src[t];
+        if (!ay.special(i0, G::NIB * CI)) {
 #pragma unroll
             for (int c = 0; c < CI; ++c) {
                 float a = 0.f;
 #pragma unroll
-                for (int l = 0; l < L; ++l) a = fmaf(wgt[c][l], hv[S * c + l], a);
+                for (int l = 0; l < L; ++l) a = fmaf(ay.c[l], hv[S * c + l], a);
                 av[c] = a;
             }
-            out(i0, lane, av);
+        } else {
+#pragma unroll
+            for (int c = 0; c < CI; ++c) {
+                const AS1 float *wb = (const AS1 float *)ay.row(i0 + ib * CI + c);
+                float a = 0.f;
+#pragma unroll
+                for (int l = 0; l < L; ++l) a = fmaf(wb[l], hv[S * c + l], a);
+                av[c] = a;
+            }
         }
+        out(ib * CI, cj, av);
     }
+    wave_lds_order();
 }
 
-// pass 3: tt[u][j] = sum_i wy[i][U - S i - offy] rs[i][j] for the TH rows.
-// PH = (U0 - offy) mod S fixes every tap offset at compile time.
+// A wave's strip of the adjoint, pass 3: tt[j][u] = sum_i wy[i][U - S i - offy]
+// rs[i][j] for the NJG LR columns its CV HR columns gather from (lanes on
+// columns x blocks of CU rows).  PH = (U0 - offy) mod S fixes every tap
+// offset at compile time.  rs holds the tile's LR rows and columns from
+// (iF, jF) on, zero outside the image; LR columns shared by neighbouring
+// waves are computed by each of them.
 template <int S, int L, int TV, int PH>
-FI void pass3_ph(const float *rs, float *tt, int U0, int offy, int iA, int iB, int NJ,
-                 const AS4 float *wyk) {
+FI void pass3_ph(const float *rs, float *tt, int U0, int offy, int iF, int jrel,
+                 const AxisW<L> &ay, int lane) {
     using T = Tile<S, L, TV>;
     constexpr int CU = T::CU, NTAP = T::NTAP;
     constexpr int NIG = (PH + CU - 1) / S + NTAP;
-    const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-    for (int ug = wv; ug * CU < T::TH; ug += kNWI) {
-        const int u0 = ug * CU;
-        const int q0 = fdiv(U0 + u0 - offy, S);
-        const int ib = q0 - (NTAP - 1);
-        // LR rows outside [0, h) read the zero padding of the table (the
-        // rows of a last tile past the image edge included: the padding
-        // after each frame covers the widest compiled tile)
-        const AS4 float *wb = wyk + ib * L;
-        float wg[CU][NTAP];
+    const int ub = lane / T::NJG, cj = lane - ub * T::NJG;
+    if (ub >= T::NUB) return;
+    const int ib = (U0 - offy - PH) / S - (NTAP - 1) + ub * (CU / S);   // (an exact division)
+    const float *src = rs + (ib - iF) * T::RP + jrel + cj;
+    float rv[NIG];
+    // LR row t contributes to row c of the block through tap PH + c + S (NTAP - 1 - t)
+#pragma unroll
+    for (int t = 0; t < NIG; ++t)
+        rv[t] = (PH + S * (NTAP - 1 - t) < L) ? src[t * T::RP] : 0.f;
+    float *dst = tt + cj * T::TS + ub * CU;
+    if (!ay.special(iF - 1, T::RSR + (T::NUB * CU - T::TH) / S + 2)) {
 #pragma unroll
         for (int c = 0; c < CU; ++c) {
             const int dq = (PH + c) / S, ph = (PH + c) % S;
+            float a = 0.f;
 #pragma unroll
-            for (int m = 0; m < NTAP; ++m) {
-                const int l = ph + S * m;
-                wg[c][m] = (l < L) ? wb[(dq - m + NTAP - 1) * L + l] : 0.f;
-            }
+            for (int m = 0; m < NTAP; ++m)
+                if (ph + S * m < L) a = fmaf(ay.c[ph + S * m], rv[dq - m + NTAP - 1], a);
+            dst[c] = a;
         }
-        if (lane < NJ) {
-            float rv[NIG];
+    } else {
 #pragma unroll
-            for (int t = 0; t < NIG; ++t) {
-                const int i = ib + t;
-                const float v = rs[(min(max(i, iA), iB) - iA) * T::NJP + lane];
-                rv[t] = (i >= iA && i <= iB) ? v : 0.f;
-            }
+        for (int c = 0; c < CU; ++c) {
+            const int dq = (PH + c) / S, ph = (PH + c) % S;
+            float a = 0.f;
 #pragma unroll
-            for (int c = 0; c < CU; ++c) {
-                const int dq = (PH + c) / S;
-                float a = 0.f;
-#pragma unroll
-                for (int m = 0; m < NTAP; ++m) a = fmaf(wg[c][m], rv[dq - m + NTAP - 1], a);
-                if (u0 + c < T::TH) tt[(u0 + c) * T::NJP + lane] = a;
-            }
+            for (int m = 0; m < NTAP; ++m)
+                if (ph + S * m < L) {
+                    const AS1 float *wb = (const AS1 float *)ay.row(ib + dq - m + NTAP - 1);
+                    a = fmaf(wb[ph + S * m], rv[dq - m + NTAP - 1], a);
+                }
+            dst[c] = a;
         }
     }
 }
 
-// pass 4: g[u][v] += sum_j wx[j][V - S j - offx] tt[u][j] for the wave's CV
-// columns; lanes take rows (u = lane - 2).
+// Pass 4: g[u][v] += sum_j wx[j][V - S j - offx] tt[j][u] for the wave's CV
+// columns; lanes take rows (u = lane - 2).  jb: the LR column of tt's first.
 template <int S, int L, int TV, int PH>
-FI void pass4_ph(const float *tt, float (&gacc)[Tile<S, L, TV>::CV], int V0, int offx, int jA,
-                 int jB, const AS4 float *wxk) {
+FI void pass4_ph(const float *tt, float (&gacc)[Tile<S, L, TV>::CV], int jb, const AxisW<L> &ax,
+                 int lane) {
     using T = Tile<S, L, TV>;
     constexpr int CV = T::CV, NTAP = T::NTAP;
     constexpr int NJG = (PH + CV - 1) / S + NTAP;
-    const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-    const int u = lane - 2;
-    const int cv0 = wv * CV;
-    const int q0 = fdiv(V0 + cv0 - offx, S);
-    const int jb = q0 - (NTAP - 1);
-    const AS4 float *wb = wxk + jb * L;
-    const int ur = min(max(u, 0), T::TH - 1);
+    const int ur = min(max(lane - 2, 0), T::TH - 1);
     float tv[NJG];
 #pragma unroll
-    for (int t = 0; t < NJG; ++t) {
-        const int j = jb + t;
-        const float v = tt[ur * T::NJP + (min(max(j, jA), jB) - jA)];
-        tv[t] = (j >= jA && j <= jB) ? v : 0.f;
-    }
+    for (int t = 0; t < NJG; ++t) tv[t] = tt[t * T::TS + ur];
+    if (!ax.special(jb, NJG)) {
 #pragma unroll
-    for (int c = 0; c < CV; ++c) {
-        const int dq = (PH + c) / S, ph = (PH + c) % S;
-        float a = 0.f;
+        for (int c = 0; c < CV; ++c) {
+            const int dq = (PH + c) / S, ph = (PH + c) % S;
+            float a = 0.f;
 #pragma unroll
-        for (int m = 0; m < NTAP; ++m) {
-            const int l = ph + S * m;
-            if (l < L) a = fmaf(wb[(dq - m + NTAP - 1) * L + l], tv[dq - m + NTAP - 1], a);
+            for (int m = 0; m < NTAP; ++m)
+                if (ph + S * m < L) a = fmaf(ax.c[ph + S * m], tv[dq - m + NTAP - 1], a);
+            gacc[c] += a;
         }
-        gacc[c] += a;
+    } else {
+#pragma unroll
+        for (int c = 0; c < CV; ++c) {
+            const int dq = (PH + c) / S, ph = (PH + c) % S;
+            float a = 0.f;
+#pragma unroll
+            for (int m = 0; m < NTAP; ++m)
+                if (ph + S * m < L)
+                    a = fmaf(ax.row(jb + dq - m + NTAP - 1)[ph + S * m], tv[dq - m + NTAP - 1], a);
+            gacc[c] += a;
+        }
     }
 }
 
-template <int S, int L, int TV>
-FI void pass3(int ph, const float *rs, float *tt, int U0, int offy, int iA, int iB, int NJ,
-              const AS4 float *wyk) {
-    if (ph == 0) pass3_ph<S, L, TV, 0>(rs, tt, U0, offy, iA, iB, NJ, wyk);
-    if constexpr (S > 1) if (ph == 1) pass3_ph<S, L, TV, 1>(rs, tt, U0, offy, iA, iB, NJ, wyk);
-    if constexpr (S > 2) if (ph == 2) pass3_ph<S, L, TV, 2>(rs, tt, U0, offy, iA, iB, NJ, wyk);
-    if constexpr (S > 3) if (ph == 3) pass3_ph<S, L, TV, 3>(rs, tt, U0, offy, iA, iB, NJ, wyk);
+// Runs f with the phase ph in [0, S) as a compile-time constant (uniform).
+template <int S, class F>
+FI void by_phase(int ph, F f) {
+    if (ph == 0) f(std::integral_constant<int, 0>{});
+    if constexpr (S > 1) if (ph == 1) f(std::integral_constant<int, 1>{});
+    if constexpr (S > 2) if (ph == 2) f(std::integral_constant<int, 2>{});
+    if constexpr (S > 3) if (ph == 3) f(std::integral_constant<int, 3>{});
 }
 
+// One frame's adjoint of the residual rs (rows and columns from (iF, jF)) into
+// the wave's CV columns; tt: the wave's own LDS.
 template <int S, int L, int TV>
-FI void pass4(int ph, const float *tt, float (&gacc)[Tile<S, L, TV>::CV], int V0, int offx, int jA,
-              int jB, const AS4 float *wxk) {
-    if (ph == 0) pass4_ph<S, L, TV, 0>(tt, gacc, V0, offx, jA, jB, wxk);
-    if constexpr (S > 1) if (ph == 1) pass4_ph<S, L, TV, 1>(tt, gacc, V0, offx, jA, jB, wxk);
-    if constexpr (S > 2) if (ph == 2) pass4_ph<S, L, TV, 2>(tt, gacc, V0, offx, jA, jB, wxk);
-    if constexpr (S > 3) if (ph == 3) pass4_ph<S, L, TV, 3>(tt, gacc, V0, offx, jA, jB, wxk);
+FI void adj_strip(const float *rs, float *tt, float (&gacc)[Tile<S, L, TV>::CV], int U0, int V0,
+                  int offy, int offx, int iF, int jF, const AxisW<L> &ay, const AxisW<L> &ax,
+                  int lane, int wv) {
+    using T = Tile<S, L, TV>;
+    const int jb = fdiv(V0 + wv * T::CV - offx, S) - (T::NTAP - 1);
+    by_phase<S>(pmod(U0 - offy, S), [&](auto ph) {
+        pass3_ph<S, L, TV, decltype(ph)::value>(rs, tt, U0, offy, iF, jb - jF, ay, lane);
+    });
+    wave_lds_order();
+    by_phase<S>(pmod(V0 - offx, S), [&](auto ph) {
+        pass4_ph<S, L, TV, decltype(ph)::value>(tt, gacc, jb, ax, lane);
+    });
+    wave_lds_order();
 }
 
 // The 8 BTV offsets d = (dx, dy) in [0, 2]^2 minus the origin (Eq. prior, w = 3).
@@ -564,9 +665,9 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
     const TileOrigin o = tile_origin<S, L, TV>(P, ty, tx);
     const int H = op.H, W = op.W, h = H / S, w = W / S, K = op.K;
     float *xs = sm;
-    float *hx = xs + T::XS;
-    float *rs = hx + T::HXS;
-    float *po = sm + T::PO;     // p at the owned pixels, for g_t . p
+    float *bands = xs + T::XS;                  // each wave's pass-1 / pass-3 output
+    float *rs = bands + kNWI * T::PWT;          // the residual, two buffers
+    float *po = sm + T::PO;                     // p at the owned pixels, for g_t . p
 
     const int xc = st.xc;
     const AS1 raw *xb = glb((const raw *)P.x[xc]);
@@ -617,7 +718,7 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
                                                       seed))
                            : ST::rnd(v);
                     if (col < T::WC) xs[row * T::WCP + col] = (rin && wc[c].in) ? vr : 0.f;
-                    if (ou >= 0 && ou < T::TH && ov >= 0 && ov < T::TW)
+                    if (T::POL && ou >= 0 && ou < T::TH && ov >= 0 && ov < T::TW)
                         po[ou * T::TW + ov] = pr[r][c];
                 }
             }
@@ -652,71 +753,80 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
     const float epsd = st.wt.eps_data, e2d = epsd * epsd;
     const AS1 rawy *yb = glb((const rawy *)P.y);
     const float yscale = st.wt.y_scale;
+    using FT = typename T::FT;
+    constexpr int CI = FT::CI, CJ = FT::CJ;
+    const int ibl = lane0 / CJ, cjl = lane0 - ibl * CJ;
+    // the frame values of pass 2, one frame ahead: each lane loads those of
+    // its own rows and column (clamped into the frame)
+    rawy yn[CI];
+    auto load_y = [&](int k) {
+        const int i = cdiv(o.U0 - L + 1 - op.offy[k], S) + ibl * CI;
+        const int j = cdiv(o.V0 - L + 1 - op.offx[k], S) + wv0 * CJ + cjl;
+        const AS1 rawy *yk = yb + (i64)k * h * w + min(max(j, 0), w - 1);
+        __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+        for (int c = 0; c < CI; ++c) yn[c] = yk[(i64)min(max(i + c, 0), h - 1) * w];
+        __builtin_amdgcn_s_setprio(0);
+    };
+    load_y(0);
     __syncthreads();
 
+    // One barrier per frame: the residual of frame k is published before the
+    // adjoint strips read it, and frame k + 1 writes the other buffer.
+    float *band = bands + wv0 * T::PWT;
     for (int k = 0; k < K; ++k) {
         const int offy = op.offy[k], offx = op.offx[k];
-        const int iA = max(0, cdiv(o.U0 - L + 1 - offy, S));
-        const int iB = min(h - 1, fdiv(o.U0 + T::TH - 1 - offy, S));
-        const int jA = max(0, cdiv(o.V0 - L + 1 - offx, S));
-        const int jB = min(w - 1, fdiv(o.V0 + T::TW - 1 - offx, S));
-        const int NI = iB - iA + 1, NJ = jB - jA + 1;
-        if (NI <= 0 || NJ <= 0) continue;
-        const AS4 float *wyk = cst(op.wy) + (i64)k * op.fsy * L;
-        const AS4 float *wxk = cst(op.wx) + (i64)k * op.fsx * L;
-        pass1<S, L, TV>(xs, S * iA + offy - o.U0 + T::EXT, S * jA + offx - o.V0 + T::EXT,
-                    S * (NI - 1) + L, NJ, wxk, jA, w - 1, hx);
-        __syncthreads();
-        const AS1 rawy *yk = yb + (i64)k * h * w;
-        pass2<S, L, TV>(hx, NI, NJ, wyk, iA, h - 1, [&](int i0, int j, const float (&av)[T::CI]) {
-            const int gj = jA + j;
-            float yv[T::CI];
-            __builtin_amdgcn_s_setprio(2);
-#pragma unroll
-            for (int c = 0; c < T::CI; ++c)
-                yv[c] = SY::ld(yk, (i64)min(iA + i0 + c, h - 1) * w + gj) * yscale;
-            __builtin_amdgcn_s_setprio(0);
+        const AxisW<L> ay = axis_y<L>(op, k), ax = axis_x<L>(op, k);
+        // LR rows and columns touching the tile (NIM x NJM from (iF, jF));
+        // those outside the frame hold a zero residual
+        const int iF = cdiv(o.U0 - L + 1 - offy, S), jF = cdiv(o.V0 - L + 1 - offx, S);
+        float *rsk = rs + (k & 1) * T::RSS;
+        const float *win =
+            xs + (S * iF + offy - o.U0 + T::EXT) * T::WCP + S * jF + offx - o.V0 + T::EXT;
+        fwd_strip<S, L, FT>(win, T::WCP, band, ay, ax, iF, jF, lane0, wv0,
+                            [&](int i0, int cj, const float (&av)[CI]) {
+            const int j = wv0 * CJ + cj, gj = jF + j;
+            const bool in_j = gj >= 0 && gj < w;
             const bool own_j = (S * gj >= o.V0) && (S * gj < P.gx0 + o.v1);
 #pragma unroll
-            for (int c = 0; c < T::CI; ++c) {
-                if (i0 + c >= NI) break;
-                const int gi = iA + i0 + c;
-                const float r = av[c] - yv[c];
+            for (int c = 0; c < CI; ++c) {
+                const int gi = iF + i0 + c;
+                const float r = fmaf(-SY::cv(yn[c]), yscale, av[c]);
                 const bool own = own_j && (S * gi >= o.U0) && (S * gi < P.gy0 + o.u1);
                 float rv;
                 if (data_p == 2) {
-                    if (own) e_data += (double)r * (double)r;
+                    const double ro = own ? (double)r : 0.0;
+                    e_data += ro * ro;
                     rv = 2.f * r;
                 } else {
                     float ph, ps;
                     phi_psi(r, epsd, e2d, ph, ps);
-                    if (own) e_data += (double)ph;
+                    e_data += own ? (double)ph : 0.0;
                     rv = ps;
                 }
-                rs[(i0 + c) * T::NJP + j] = rv;
+                rsk[(i0 + c) * T::RP + j] = (in_j && gi >= 0 && gi < h) ? rv : 0.f;
             }
         });
+        if (k + 1 < K) load_y(k + 1);
         __syncthreads();
-        pass3<S, L, TV>(pmod(o.U0 - offy, S), rs, hx, o.U0, offy, iA, iB, NJ, wyk);
-        __syncthreads();
-        pass4<S, L, TV>(pmod(o.V0 - offx, S), hx, gacc, o.V0, offx, jA, jB, wxk);
-        __syncthreads();
+        adj_strip<S, L, TV>(rsk, band, gacc, o.U0, o.V0, offy, offx, iF, jF, ay, ax, lane0, wv0);
     }
+    __syncthreads();
 
     // data-term gradient to LDS (lanes hold rows), then the prior adds in place
-    float *gs = hx;
+    float *gs = bands;
     {
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        const int u = lane - 2;
+        const int u = lane0 - 2;
         if (u >= 0 && u < T::TH)
 #pragma unroll
-            for (int c = 0; c < T::CV; ++c) gs[u * T::GP + wv * T::CV + c] = gacc[c];
+            for (int c = 0; c < T::CV; ++c) gs[u * T::GP + wv0 * T::CV + c] = gacc[c];
     }
     // the output pass's loads of g_k are issued here, so that they are in
     // flight during the prior's sweep (p at the owned pixels is in LDS)
     const int cur = st.cur;
     AS1 float *gout = glbw(P.g[cur ^ 1]);
     const AS1 float *gk = glb(P.g[cur]);
+    const AS1 float *pk = glb(P.p[xc]);
     AS1 float *pz = glbw(P.p[xc]);
     // owned pixels by rows as in the staging: wave wv0 takes tile rows
     // wv0 + kNWI r, lane takes columns lane0 + 64 c
@@ -788,7 +898,7 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
             if (mode == 0 && pz) pz[rb + ocol[c]] = 0.f;
             if (mode == 1) {
                 ggk += (double)gv * (double)gkv[r][c];
-                gp += (double)gv * (double)po[row * T::TW + col];
+                gp += (double)gv * (double)(T::POL ? po[row * T::TW + col] : pk[rb + ocol[c]]);
             }
         }
     }
@@ -799,52 +909,49 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
 // Data part of the curvature over the owned LR pixels (all edges are
 // multiples of S): L2 (DP = 2), 2 |A_k p|^2, exact since the term is
 // quadratic; L1 (DP = 1, Charbonnier), the sum of (A_k p)^2 Q(r, sk A_k p) with
-// r = A_k x - y_k and Q the quotient the prior's pairs use.
+// r = A_k x - y_k and Q the quotient the prior's pairs use.  Each wave runs
+// its own strip of every frame with no barrier; [iA, iB) x [jA, jB) are the
+// owned LR pixels.
 template <int S, int L, int TV, class SY, int DP>
 FI double upd_data_part(const AS4 Proj &P, const AS4 ScgState &st, const TileOrigin &o,
-                        const float *xs, const float *ps, float *hx, float *ax, int NIo,
-                        int NJo, int iA, int jA) {
+                        const float *xs, const float *ps, float *band, int iA, int iB, int jA,
+                        int jB, int lane, int wv) {
     using T = Tile<S, L, TV>;
+    using FU = typename T::FU;
     using rawy = typename SY::raw;
     const AS4 OpDev &op = *cst(P.op);
     const int h = op.H / S, w = op.W / S, K = op.K;
     const float skd = st.sigk_f, epsd = st.wt.eps_data, e2d = epsd * epsd;
     const AS1 rawy *yb = glb((const rawy *)P.y);
+    const int i0t = o.U0 / S, j0t = o.V0 / S;
     double ap2 = 0.0;
     for (int k = 0; k < K; ++k) {
-        const int offy = op.offy[k], offx = op.offx[k];
-        const AS4 float *wyk = cst(op.wy) + (i64)k * op.fsy * L;
-        const AS4 float *wxk = cst(op.wx) + (i64)k * op.fsx * L;
-        if (DP == 1) {
-            pass1<S, L, TV>(xs, S * iA + offy - o.U0 + T::EXT, S * jA + offx - o.V0 + T::EXT,
-                        S * (NIo - 1) + L, NJo, wxk, jA, w - 1, hx);
-            __syncthreads();
-            pass2<S, L, TV>(hx, NIo, NJo, wyk, iA, h - 1, [&](int i0, int j, const float (&av)[T::CI]) {
+        const int woff = (op.offy[k] + T::EXT) * T::WCP + op.offx[k] + T::EXT;
+        const AxisW<L> ay = axis_y<L>(op, k), ax = axis_x<L>(op, k);
+        float xa[FU::CI];
+        if (DP == 1)
+            fwd_strip<S, L, FU>(xs + woff, T::WCP, band, ay, ax, i0t, j0t, lane, wv,
+                                [&](int, int, const float (&av)[FU::CI]) {
 #pragma unroll
-                for (int c = 0; c < T::CI; ++c)
-                    if (i0 + c < NIo) ax[(i0 + c) * T::NJP + j] = av[c];
+                for (int c = 0; c < FU::CI; ++c) xa[c] = av[c];
             });
-            __syncthreads();
-        }
-        pass1<S, L, TV>(ps, S * iA + offy - o.U0 + T::EXT, S * jA + offx - o.V0 + T::EXT,
-                    S * (NIo - 1) + L, NJo, wxk, jA, w - 1, hx);
-        __syncthreads();
         const AS1 rawy *yk = yb + (i64)k * h * w;
-        pass2<S, L, TV>(hx, NIo, NJo, wyk, iA, h - 1, [&](int i0, int j, const float (&av)[T::CI]) {
+        fwd_strip<S, L, FU>(ps + woff, T::WCP, band, ay, ax, i0t, j0t, lane, wv,
+                            [&](int i0, int cj, const float (&av)[FU::CI]) {
+            const int gj = j0t + wv * FU::CJ + cj;
 #pragma unroll
-            for (int c = 0; c < T::CI; ++c) {
-                if (i0 + c >= NIo) break;
+            for (int c = 0; c < FU::CI; ++c) {
+                const int gi = i0t + i0 + c;
+                const bool own = gj >= jA && gj < jB && gi >= iA && gi < iB;
                 if (DP == 2) {
-                    ap2 += (double)av[c] * (double)av[c];
-                } else {
-                    const float r = ax[(i0 + c) * T::NJP + j] -
-                                    SY::ld(yk, (i64)(iA + i0 + c) * w + jA + j) *
-                                        st.wt.y_scale;
+                    const double a = own ? (double)av[c] : 0.0;
+                    ap2 += a * a;
+                } else if (own) {
+                    const float r = fmaf(-SY::ld(yk, (i64)gi * w + gj), st.wt.y_scale, xa[c]);
                     ap2 += (double)(av[c] * av[c] * psi_quot(r, skd * av[c], epsd, e2d));
                 }
             }
         });
-        __syncthreads();
     }
     return DP == 2 ? 2.0 * ap2 : ap2;
 }
@@ -877,11 +984,10 @@ FI void tile_upcurv(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, f
     o.V0 = P.gx0 + o.v0;
     const int ou0 = max(o.u0, P.oy0), ou1 = min(o.u1, P.oy1);
     const int ov0 = max(o.v0, P.ox0), ov1 = min(o.v1, P.ox1);
-    const int H = op.H, W = op.W, h = H / S, w = W / S, K = op.K;
+    const int H = op.H, W = op.W;
     float *xs = sm;
     float *ps = xs + T::XS;
-    float *hx = ps + T::XS;
-    float *ax = hx + T::HXS;    // A_k x at the owned LR pixels (L1 data term)
+    float *bands = ps + T::XS;  // each wave's pass-1 output
 
     const int src = st.upd_src, dst = src ^ 1;
     const AS1 raw *xb = glb((const raw *)P.x[src]);
@@ -958,14 +1064,15 @@ FI void tile_upcurv(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, f
     // (A_k p)^2 Q(r, sk A_k p) with r = A_k x - y_k, the same quotient as the
     // prior's pairs
     double ap2 = 0.0;
-    const int NIo = (ou1 - ou0) / S, NJo = (ov1 - ov0) / S;
-    const int iA = (P.gy0 + ou0) / S, jA = (P.gx0 + ov0) / S;
-    const int data_p = st.wt.data_p;
-    if (NIo > 0 && NJo > 0) {
-        if (data_p == 2)
-            ap2 = upd_data_part<S, L, TV, SY, 2>(P, st, o, xs, ps, hx, ax, NIo, NJo, iA, jA);
+    const int lane = tid & 63, wv = uni(tid >> 6);
+    const int iA = (P.gy0 + ou0) / S, iB = (P.gy0 + ou1) / S;
+    const int jA = (P.gx0 + ov0) / S, jB = (P.gx0 + ov1) / S;
+    float *band = bands + wv * T::FU::LDS;
+    if (iA < iB && jA < jB) {
+        if (st.wt.data_p == 2)
+            ap2 = upd_data_part<S, L, TV, SY, 2>(P, st, o, xs, ps, band, iA, iB, jA, jB, lane, wv);
         else
-            ap2 = upd_data_part<S, L, TV, SY, 1>(P, st, o, xs, ps, hx, ax, NIo, NJo, iA, jA);
+            ap2 = upd_data_part<S, L, TV, SY, 1>(P, st, o, xs, ps, band, iA, iB, jA, jB, lane, wv);
     }
     // prior part over the owned pairs (i, i+d)
     const float eps = st.wt.eps, sk = st.sigk_f;
@@ -1002,7 +1109,6 @@ FI void tile_forward(const AS4 Proj &P, int ty, int tx, void *yout, float *sm) {
     const TileOrigin o = tile_origin<S, L, TV>(P, ty, tx);
     const int h = op.H / S, w = op.W / S, K = op.K;
     float *xs = sm;
-    float *hx = xs + T::XS;
     const AS1 raw *xb = glb((const raw *)P.x[0]);
     const int Hb = P.Hb, Wb = P.Wb, ld = P.ld;
     for (int q = tid; q < T::WR * T::WC; q += kNTI) {
@@ -1015,21 +1121,21 @@ FI void tile_forward(const AS4 Proj &P, int ty, int tx, void *yout, float *sm) {
     __syncthreads();
     const int NIo = (o.u1 - o.u0) / S, NJo = (o.v1 - o.v0) / S;
     const int iA = o.U0 / S, jA = o.V0 / S;
-    if (NIo <= 0 || NJo <= 0) return;
+    using FU = typename T::FU;
+    const int lane = tid & 63, wv = uni(tid >> 6);
+    float *band = xs + T::XS + wv * FU::LDS;
     AS1 raw *yo = glbw((raw *)yout);
     for (int k = 0; k < K; ++k) {
-        const int offy = op.offy[k], offx = op.offx[k];
-        const AS4 float *wyk = cst(op.wy) + (i64)k * op.fsy * L;
-        const AS4 float *wxk = cst(op.wx) + (i64)k * op.fsx * L;
-        pass1<S, L, TV>(xs, offy + T::EXT, offx + T::EXT, S * (NIo - 1) + L, NJo, wxk, jA, w - 1, hx);
-        __syncthreads();
-        const i64 yb = (i64)k * h * w;
-        pass2<S, L, TV>(hx, NIo, NJo, wyk, iA, h - 1, [&](int i0, int j, const float (&av)[T::CI]) {
+        const AxisW<L> ay = axis_y<L>(op, k), ax = axis_x<L>(op, k);
+        const float *win = xs + (op.offy[k] + T::EXT) * T::WCP + op.offx[k] + T::EXT;
+        fwd_strip<S, L, FU>(win, T::WCP, band, ay, ax, iA, jA, lane, wv,
+                            [&](int i0, int cj, const float (&av)[FU::CI]) {
+            const int j = wv * FU::CJ + cj;
+            const i64 at = ((i64)k * h + iA + i0) * w + jA + j;
 #pragma unroll
-            for (int c = 0; c < T::CI; ++c)
-                if (i0 + c < NIo) ST::st(yo, yb + (i64)(iA + i0 + c) * w + jA + j, av[c]);
+            for (int c = 0; c < FU::CI; ++c)
+                if (j < NJo && i0 + c < NIo) ST::st(yo, at + (i64)c * w, av[c]);
         });
-        __syncthreads();
     }
 }
 
@@ -1046,34 +1152,46 @@ FI void tile_adjoint(const AS4 Proj &P, int ty, int tx, const void *r, float *xo
     const TileOrigin o = tile_origin<S, L, TV>(P, ty, tx);
     const int h = op.H / S, w = op.W / S, K = op.K;
     float *gs = sm;
-    float *tt = gs + T::XS;
-    float *rs = tt + T::HXS;
+    const int lane = tid & 63, wv = uni(tid >> 6);
+    float *band = gs + T::XS + wv * T::PWT;
+    float *rs = gs + T::XS + kNWI * T::PWT;
     const AS1 raw *rb = glb((const raw *)r);
     float gacc[T::CV];
 #pragma unroll
     for (int c = 0; c < T::CV; ++c) gacc[c] = 0.f;
+    // the LR rows and columns touching the tile, NIM x NJM from (iF, jF), one
+    // frame ahead in registers; zero outside the frame
+    constexpr int NQ = ceil_div(T::NIM * T::NJM, kNTI);
+    float rn[NQ];
+    auto load_r = [&](int k) {
+        const int iF = cdiv(o.U0 - L + 1 - op.offy[k], S);
+        const int jF = cdiv(o.V0 - L + 1 - op.offx[k], S);
+#pragma unroll
+        for (int e = 0; e < NQ; ++e) {
+            const int q = tid + e * kNTI, ii = q / T::NJM, jj = q - ii * T::NJM;
+            const int gi = iF + ii, gj = jF + jj;
+            const bool in = gi >= 0 && gi < h && gj >= 0 && gj < w;
+            const float v = ST::ld(rb, ((i64)k * h + min(max(gi, 0), h - 1)) * w +
+                                           min(max(gj, 0), w - 1));
+            rn[e] = in ? v : 0.f;
+        }
+    };
+    load_r(0);
     for (int k = 0; k < K; ++k) {
         const int offy = op.offy[k], offx = op.offx[k];
-        const int iA = max(0, cdiv(o.U0 - L + 1 - offy, S));
-        const int iB = min(h - 1, fdiv(o.U0 + T::TH - 1 - offy, S));
-        const int jA = max(0, cdiv(o.V0 - L + 1 - offx, S));
-        const int jB = min(w - 1, fdiv(o.V0 + T::TW - 1 - offx, S));
-        const int NI = iB - iA + 1, NJ = jB - jA + 1;
-        if (NI <= 0 || NJ <= 0) continue;
-        const AS4 float *wyk = cst(op.wy) + (i64)k * op.fsy * L;
-        const AS4 float *wxk = cst(op.wx) + (i64)k * op.fsx * L;
-        for (int q = tid; q < NI * T::NJP; q += kNTI) {
-            const int ii = q / T::NJP, jj = q - ii * T::NJP;
-            if (jj < NJ) rs[q] = ST::ld(rb, (i64)k * h * w + (i64)(iA + ii) * w + jA + jj);
+        const AxisW<L> ay = axis_y<L>(op, k), ax = axis_x<L>(op, k);
+        const int iF = cdiv(o.U0 - L + 1 - offy, S), jF = cdiv(o.V0 - L + 1 - offx, S);
+        float *rsk = rs + (k & 1) * T::RSS;
+#pragma unroll
+        for (int e = 0; e < NQ; ++e) {
+            const int q = tid + e * kNTI, ii = q / T::NJM, jj = q - ii * T::NJM;
+            if (ii < T::NIM) rsk[ii * T::RP + jj] = rn[e];
         }
+        if (k + 1 < K) load_r(k + 1);
         __syncthreads();
-        pass3<S, L, TV>(pmod(o.U0 - offy, S), rs, tt, o.U0, offy, iA, iB, NJ, wyk);
-        __syncthreads();
-        pass4<S, L, TV>(pmod(o.V0 - offx, S), tt, gacc, o.V0, offx, jA, jB, wxk);
-        __syncthreads();
+        adj_strip<S, L, TV>(rsk, band, gacc, o.U0, o.V0, offy, offx, iF, jF, ay, ax, lane, wv);
     }
     {
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
         const int u = lane - 2;
         if (u >= 0 && u < T::TH)
 #pragma unroll
@@ -1126,7 +1244,7 @@ __global__ void __launch_bounds__(kNTI, 4) k_trial(const Proj *projs, const Item
 template <int S, int L, int TV, class ST, class SY>
 __global__ void __launch_bounds__(kNTI, 4) k_upcurv(const Proj *projs, const Item *items,
                                                  const int *n_items, double *partials) {
-    __shared__ float sm[Tile<S, L, TV>::SMEM];
+    __shared__ float sm[Tile<S, L, TV>::SMEM_U];
     __shared__ double red[kNV * kNWI];
     const int n = *cst(n_items);
     const int b = blockIdx.x;
@@ -1142,7 +1260,7 @@ __global__ void __launch_bounds__(kNTI, 4) k_upcurv(const Proj *projs, const Ite
 template <int S, int L, int TV, class ST>
 __global__ void __launch_bounds__(kNTI) k_forward(const Proj *projs, const Item *items, int n,
                                                   void *yout) {
-    __shared__ float sm[Tile<S, L, TV>::SMEM];
+    __shared__ float sm[Tile<S, L, TV>::SMEM_F];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const AS4 Item &itm = cst(items)[it];
         tile_forward<S, L, TV, ST>(cst(projs)[itm.proj], itm.ty, itm.tx, yout, sm);
@@ -1153,7 +1271,7 @@ __global__ void __launch_bounds__(kNTI) k_forward(const Proj *projs, const Item 
 template <int S, int L, int TV, class ST>
 __global__ void __launch_bounds__(kNTI) k_adjoint(const Proj *projs, const Item *items, int n,
                                                   const void *r, float *xout) {
-    __shared__ float sm[Tile<S, L, TV>::SMEM];
+    __shared__ float sm[Tile<S, L, TV>::SMEM_A];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const AS4 Item &itm = cst(items)[it];
         tile_adjoint<S, L, TV, ST>(cst(projs)[itm.proj], itm.ty, itm.tx, r, xout, sm);

@@ -27,7 +27,10 @@ constexpr int st_y(int code) { return code >> 4; }
 // frame's rows and fsy - h - kPadRows (fsx - w - kPadRows) after them, so
 // that kernels may index outside [0, h): the adjoint passes compute whole
 // tiles, and a last tile past the image edge reads rows up to about a tile
-// extent / s beyond it (band_pad_after).
+// extent / s beyond it (band_pad_after).  cwy[k] / cwx[k]: the weights of the
+// LR rows the image edge does not cut, which are all alike: rows
+// [loy[k], hiy[k]) (columns [lox[k], hix[k])) equal them at every HR row
+// (column) inside the image, the others (a few at either edge) do not.
 //
 // General operators (affine warps or non-separable PSFs, where A_k does not
 // factor; wy/wx are then NULL) are evaluated from their factors (mf = 1):
@@ -50,6 +53,8 @@ struct OpDev {
     int offx[kMaxK];
     int H, W, s, K, L;
     int fsy, fsx;        // frame stride of wy / wx in rows (padding included)
+    int loy[kMaxK], hiy[kMaxK], lox[kMaxK], hix[kMaxK];
+    float cwy[kMaxK][kMaxL], cwx[kMaxK][kMaxL];
     int a_w, t_w;
     const int *a_col;
     const float *a_val;
