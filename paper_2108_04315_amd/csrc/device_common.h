@@ -130,7 +130,22 @@ FI void phi_psi(float z, float eps, float e2, float &phi, float &psi) {
 //   (e^2 + C) / (A B (A + B)),  A = |(a, e)|, B = |(b, e)|, C = A B - a b,
 // with C = (e^2 (a^2 + b^2) + e^4) / (A B + a b) when a b > 0.  When |h| is
 // below 1e-3 B the Taylor series in h to third order is used instead (its
-// remainder is below float32 rounding).
+// remainder is below float32 rounding).  rB = 1 / B.
+FI float psi_series(float b, float h, float rB, float e2) {
+    const float rB2 = rB * rB;
+    const float t = h * rB2;
+    const float poly = fmaf(0.5f * t * t, fmaf(4.f * b, b, -e2), fmaf(-1.5f * t, b, 1.f));
+    return e2 * rB * rB2 * poly;
+}
+FI float psi_closed(float b, float h, float rB, float e2) {
+    const float a = b + h;
+    const float aa = fmaf(a, a, e2);
+    const float rA = rsq(aa);
+    const float A = aa * rA, B = fmaf(b, b, e2) * rB;
+    const float AB = A * B, ab = a * b;
+    const float C = (ab > 0.f) ? (e2 * (a * a + b * b) + e2 * e2) / (AB + ab) : AB - ab;
+    return (e2 + C) * rA * rB / (A + B);
+}
 FI float psi_quot(float b, float h, float eps, float e2) {
     if (eps == 0.f) {
         if (h == 0.f) return 0.f;
@@ -139,21 +154,8 @@ FI float psi_quot(float b, float h, float eps, float e2) {
         const float sb = (b > 0.f) ? 1.f : ((b < 0.f) ? -1.f : 0.f);
         return (sa - sb) / h;
     }
-    const float bb = fmaf(b, b, e2);
-    const float rB = rsq(bb);
-    const float rB2 = rB * rB;
-    const float t = h * rB2;
-    if (fabsf(h * rB) < 1e-3f) {
-        const float poly = fmaf(0.5f * t * t, fmaf(4.f * b, b, -e2), fmaf(-1.5f * t, b, 1.f));
-        return e2 * rB * rB2 * poly;
-    }
-    const float a = b + h;
-    const float aa = fmaf(a, a, e2);
-    const float rA = rsq(aa);
-    const float A = aa * rA, B = bb * rB;
-    const float AB = A * B, ab = a * b;
-    const float C = (ab > 0.f) ? (e2 * (a * a + b * b) + e2 * e2) / (AB + ab) : AB - ab;
-    return (e2 + C) * rA * rB / (A + B);
+    const float rB = rsq(fmaf(b, b, e2));
+    return fabsf(h * rB) < 1e-3f ? psi_series(b, h, rB, e2) : psi_closed(b, h, rB, e2);
 }
 
 FI double wave_sum(double v) {

@@ -23,7 +23,7 @@
 // of their chain (LDS round trips, barriers, scalar loads) and VALU issue: one
 // barrier instead of four per frame and no per-row weight loads took the
 // standalone adjoint of 9 frames of 1024^2 at x3 from 157 to 98 us, k_trial
-// from 64.6 to 56.5 us at 2048^2 x2 (4 frames) and from 779 to 537 us at
+// from 64.6 to 56.6 us at 2048^2 x2 (4 frames) and from 779 to 569 us at
 // 6144^2 x3 (9 frames).
 #include <hip/hip_runtime.h>
 
@@ -485,40 +485,35 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
 
 // Curvature of the prior along p (Moller's step 2 without forming x + sk p):
 // sum over owned pairs of gamma q^2 Q(z, sk q), z, q the pair differences of
-// x and p.  Same sweep as btv_sweep (lanes on rows, waves on CV columns,
-// 3-slot rotating windows, unrolled by three); [ru0,ru1) x [rv0,rv1) is the
-// owned part of the tile.  With eps > 0 every pair first takes the
-// first-order series of psi_quot, Q(z, h) = eps^2 / B^3 (1 - 3/2 h z / B^2),
-// B = |(z, eps)|: in u = q / B the term is gamma eps^2 u^2 / B times
-// (1 - 3/2 sk u z / B).  The next term of the series is at most 2 (h / B)^2
-// relative, so for |h| / B = sk |u| < kCurvTau = 1e-4 the truncation stays
-// below FP32 rounding; a lane with a pair beyond that recomputes its column
-// with the closed form, so the common case takes one branch per column.
+// x and p; [ru0,ru1) x [rv0,rv1) is the owned part of the tile.  With eps > 0
+// every pair first takes the first-order series of psi_quot, Q(z, h) =
+// eps^2 / B^3 (1 - 3/2 h z / B^2), B = |(z, eps)|: in u = q / B the term is
+// gamma eps^2 u^2 / B times (1 - 3/2 sk u z / B).  The next term of the series
+// is at most 2 (h / B)^2 relative, so for |h| / B = sk |u| < kCurvTau = 1e-4
+// the truncation stays below FP32 rounding; a pixel with a pair beyond that
+// sums its pairs again, those beyond by psi_quot (its series; the closed form
+// runs only where a pair needs it), so the common case takes one branch per
+// pixel.
+//
+// VALU issue bounds the sweep (about 13 operations and a reciprocal root per
+// pair).  A step takes NC neighbouring columns of NRB rows RS apart, NC NRB =
+// 64, so that every lane owns a pixel (48 x 96 tile: 72 steps of 64 pixels;
+// lanes on the 48 rows of one column took 96), and a pixel needs nothing from
+// its neighbours but the LDS windows.  Images whose flat parts send half of
+// the pixels beyond the series (128^2) recomputed the whole pixel with both
+// branches of psi_quot before.  k_upcurv: 49.9 ->
+// 45.1 us at 2048^2, 25.0 -> 21.1 us at 128^2 (six tiles, one per CU).
 template <int S, int L, int TV, bool CHECK, bool EPS0>
 FI void curv_sweep(const float *xs, const float *ps, const float (&gam)[8], float eps, float sk,
                    int U0, int V0, int H, int W, int ru0, int ru1, int rv0, int rv1,
                    double &dreg) {
     using T = Tile<S, L, TV>;
-    constexpr int NSTEP = T::CV;
+    constexpr int NC = T::TW % 32 == 0 ? 32 : (T::TW % 16 == 0 ? 16 : 8), NRB = 64 / NC;
+    constexpr int RS = ceil_div(T::TH, NRB), NST = T::TW / NC * RS, SPW = ceil_div(NST, kNWI);
+    static_assert(T::TW % NC == 0, "whole column groups");
     const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
-    const int u = lane;
-    const int cv0 = wv * T::CV;
-    const int U = U0 + u;
-    const int ur = min(u, T::TH - 1);
+    const int cl = lane % NC, ul = lane / NC * RS;
     const float e2 = eps * eps;
-    const bool own_row = CHECK ? (u >= ru0 && u < ru1) : (u < T::TH);
-    bool rok[3];
-#pragma unroll
-    for (int dy = 0; dy < 3; ++dy) rok[dy] = !CHECK || (U + dy < H);
-    const int off = (T::EXT + ur) * T::WCP + T::EXT + cv0;
-    float wx[3][3], wp[3][3];   // [dy][slot]: window column c in slot c % 3
-#pragma unroll
-    for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-        for (int dx = 0; dx < 2; ++dx) {
-            wx[dy][dx] = xs[off + dy * T::WCP + dx];
-            wp[dy][dx] = ps[off + dy * T::WCP + dx];
-        }
     float gq[8];   // gamma_d eps^2
 #pragma unroll
     for (int d = 0; d < 8; ++d) gq[d] = gam[d] * e2;
@@ -526,83 +521,63 @@ FI void curv_sweep(const float *xs, const float *ps, const float (&gam)[8], floa
     const float c15 = -1.5f * sk;
     const float umax_ok = kCurvTau / sk;   // sk |u| < tau  <=>  |u| < tau / sk
     double acc = 0.0;
-    // step t handles column cv0 + t and loads window column t + 2 (slot (t+2) % 3)
-    auto step = [&](auto slot_c, int t) {
-        constexpr int Q = decltype(slot_c)::value;   // slot of column t
+    const int s1 = min((wv + 1) * SPW, NST);
+    for (int st = wv * SPW; st < s1; ++st) {
+        const int g = st / RS, r = st - g * RS;   // column group, row within each block
+        const int u = ul + r, v = g * NC + cl;
+        const int off = (T::EXT + (NRB * RS > T::TH ? min(u, T::TH - 1) : u)) * T::WCP + T::EXT + v;
+        float wx[3][3], wp[3][3];
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-            wx[dy][(Q + 2) % 3] = xs[off + dy * T::WCP + t + 2];
-            wp[dy][(Q + 2) % 3] = ps[off + dy * T::WCP + t + 2];
-        }
-        const int v = cv0 + t, V = V0 + v;
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                wx[dy][dx] = xs[off + dy * T::WCP + dx];
+                wp[dy][dx] = ps[off + dy * T::WCP + dx];
+            }
+        // pair validity (both pixels inside the image)
+        const int U = U0 + u, V = V0 + v;
+        bool ok[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) ok[d] = !CHECK || (U + kDY[d] < H && V + kDX[d] < W);
         float a = 0.f;
         if (EPS0) {
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
-                const int dx = kDX[d], dy = kDY[d];
-                const float z = wx[0][Q] - wx[dy][(Q + dx) % 3];
-                const float qd = wp[0][Q] - wp[dy][(Q + dx) % 3];
+                const float z = wx[0][0] - wx[kDY[d]][kDX[d]];
+                const float qd = wp[0][0] - wp[kDY[d]][kDX[d]];
                 const float tq = gam[d] * qd * qd * psi_quot(z, sk * qd, eps, e2);
-                if (CHECK)
-                    a += (rok[dy] && V + dx < W) ? tq : 0.f;
-                else
-                    a += tq;
+                a += ok[d] ? tq : 0.f;
             }
         } else {
-            float umax = 0.f;
+            float z[8], qd[8], rB[8], uu[8], tq[8], umax = 0.f;
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
-                const int dx = kDX[d], dy = kDY[d];
-                const float z = wx[0][Q] - wx[dy][(Q + dx) % 3];
-                const float qd = wp[0][Q] - wp[dy][(Q + dx) % 3];
-                const float rB = rsq(fmaf(z, z, e2));
-                const float u = qd * rB;
-                const float poly = fmaf(c15, u * (z * rB), 1.f);
-                const float tq = (u * u) * rB * poly;
-                umax = fmaxf(umax, fabsf(u));
-                if (CHECK)
-                    a = fmaf((rok[dy] && V + dx < W) ? gq[d] : 0.f, tq, a);
-                else
-                    a = fmaf(gq[d], tq, a);
+                z[d] = wx[0][0] - wx[kDY[d]][kDX[d]];
+                qd[d] = wp[0][0] - wp[kDY[d]][kDX[d]];
+                rB[d] = rsq(fmaf(z[d], z[d], e2));
+                uu[d] = qd[d] * rB[d];
+                const float poly = fmaf(c15, uu[d] * (z[d] * rB[d]), 1.f);
+                tq[d] = (uu[d] * uu[d]) * rB[d] * poly;
+                umax = fmaxf(umax, fabsf(uu[d]));
+                a = fmaf(ok[d] ? gq[d] : 0.f, tq[d], a);
             }
             if (!(umax < umax_ok)) {
-                // some pair is beyond the series' range: the column again,
-                // each such pair with the closed form
                 a = 0.f;
 #pragma unroll
                 for (int d = 0; d < 8; ++d) {
-                    const int dx = kDX[d], dy = kDY[d];
-                    const float z = wx[0][Q] - wx[dy][(Q + dx) % 3];
-                    const float qd = wp[0][Q] - wp[dy][(Q + dx) % 3];
-                    const float rB = rsq(fmaf(z, z, e2));
-                    const float u = qd * rB;
-                    float tq;
-                    if (fabsf(u) < umax_ok)
-                        tq = gq[d] * ((u * u) * rB * fmaf(c15, u * (z * rB), 1.f));
-                    else
-                        tq = gam[d] * qd * qd * psi_quot(z, sk * qd, eps, e2);
-                    if (CHECK)
-                        a += (rok[dy] && V + dx < W) ? tq : 0.f;
-                    else
-                        a += tq;
+                    const float h = sk * qd[d];
+                    const bool far = !(fabsf(uu[d]) < umax_ok);
+                    float q = psi_series(z[d], h, rB[d], e2);
+                    if (far && !(fabsf(h * rB[d]) < 1e-3f)) q = psi_closed(z[d], h, rB[d], e2);
+                    const float tf = far ? gam[d] * qd[d] * qd[d] * q : gq[d] * tq[d];
+                    a += ok[d] ? tf : 0.f;
                 }
             }
         }
-        const bool own = own_row && (!CHECK || (v >= rv0 && v < rv1));
+        const bool own = CHECK ? (u >= ru0 && u < ru1 && v >= rv0 && v < rv1)
+                               : (NRB * RS == T::TH || u < T::TH);
         acc += own ? (double)a : 0.0;
-    };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-#pragma unroll 1
-    for (int t = 0; t + 2 < NSTEP; t += 3) {
-        step(I0{}, t);
-        step(I1{}, t + 1);
-        step(I2{}, t + 2);
     }
-    constexpr int REM = NSTEP % 3;
-    if constexpr (REM >= 1) step(I0{}, NSTEP - REM);
-    if constexpr (REM >= 2) step(I1{}, NSTEP - REM + 1);
     dreg += acc;
 }
 
