@@ -253,22 +253,40 @@ __global__ void k_finalize(const Proj *__restrict__ projs, int nproj, int stype)
 
 // ---------------------------------------------------- tiled-solve helpers
 // Halo exchange: each copy moves a rectangle of the trial gradient g[cur^1]
-// from the view that owns it into another view's halo.
-__global__ void k_halo(const Proj *__restrict__ projs, const HaloCopy *__restrict__ copies,
-                       const int *n_copies) {
+// from the view that owns it into another view's halo.  A copy between two
+// neighbours is a strip as long as the view (2048 x 16 HR px at 1024^2-LR tiles
+// with a halo of 8) and moves few bytes per launch, so the launch is bound by
+// how many loads are in flight: kHaloPx pixels of a rectangle per workgroup
+// (blockIdx.y), every load before the first store.
+// One workgroup per copy took 74.8 us on four such tiles; this takes 8.1.
+constexpr int kHaloPx = 2048;   // pixels per workgroup
+__global__ void __launch_bounds__(256) k_halo(const Proj *__restrict__ projs,
+                                              const HaloCopy *__restrict__ copies,
+                                              const int *n_copies) {
     const int n = *n_copies;
     for (int c = blockIdx.x; c < n; c += gridDim.x) {
         const HaloCopy hc = copies[c];
         const Proj &A = projs[hc.src];
         const Proj &B = projs[hc.dst];
         const int g = A.st->cur ^ 1;
-        const float *src = A.g[g];
-        float *dst = B.g[g];
-        for (int q = threadIdx.x; q < hc.rows * hc.cols; q += blockDim.x) {
-            const int r = q / hc.cols, cc = q - r * hc.cols;
-            const int gy = hc.gy + r, gx = hc.gx + cc;
-            dst[(long long)(gy - B.gy0) * B.ld + gx - B.gx0] =
-                src[(long long)(gy - A.gy0) * A.ld + gx - A.gx0];
+        const long long lda = A.ld, ldb = B.ld;
+        const float *__restrict__ src =
+            A.g[g] + (long long)(hc.gy - A.gy0) * lda + hc.gx - A.gx0;
+        float *__restrict__ dst = B.g[g] + (long long)(hc.gy - B.gy0) * ldb + hc.gx - B.gx0;
+        const unsigned px = (unsigned)hc.rows * (unsigned)hc.cols;   // < 2^31, as the image
+        for (unsigned q0 = blockIdx.y * kHaloPx; q0 < px; q0 += gridDim.y * kHaloPx) {
+            float v[kHaloPx / 256];
+            long long at[kHaloPx / 256];
+#pragma unroll
+            for (int e = 0; e < kHaloPx / 256; ++e) {
+                const unsigned q = q0 + e * 256 + threadIdx.x;
+                const unsigned r = q / (unsigned)hc.cols, cc = q - r * (unsigned)hc.cols;
+                at[e] = q < px ? r * ldb + cc : -1;
+                if (q < px) v[e] = src[r * lda + cc];
+            }
+#pragma unroll
+            for (int e = 0; e < kHaloPx / 256; ++e)
+                if (at[e] >= 0) dst[at[e]] = v[e];
         }
     }
 }
@@ -505,7 +523,7 @@ hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, con
 hipError_t launch_halo(hipStream_t stream, const Proj *projs, const HaloCopy *copies,
                        const int *n_copies, int grid) {
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_halo, dim3(grid), dim3(256), 0, stream, projs, copies, n_copies);
+    hipLaunchKernelGGL(k_halo, dim3(grid, 32), dim3(256), 0, stream, projs, copies, n_copies);
     return hipGetLastError();
 }
 
