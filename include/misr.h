@@ -229,7 +229,9 @@ misr_status misr_op_tune(misr_op *op, const misr_params *params, const void *y, 
                          int reps, int32_t *tile_h, int32_t *tile_w, void *stream);
 /* The operator's current tile shape of the update pass and the operators
  * (HR pixels; 0 x 0 for a general operator); the trial pass's tile has the
- * same height. */
+ * same height.  An operator that was neither tuned nor set and whose image is
+ * small (fewer narrow tiles than would fill the chip) runs narrower tiles of
+ * the same height; the shape reported stays the variant's. */
 misr_status misr_op_tile(const misr_op *op, int32_t *tile_h, int32_t *tile_w);
 /* The operator's current tile variant (-1 for a general operator) and the
  * width of its trial-pass tile in HR pixels. */

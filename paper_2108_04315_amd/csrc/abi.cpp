@@ -609,6 +609,32 @@ void misr::band_pad_after(int S, int Lp, int &pad_y, int &pad_x) {
     pad_x = std::max(kPadRows, (tw + tw / 8 + Lp + 2 * S) / S + 2);
 }
 
+// An image takes the narrow tiles while they are so few that the wide ones
+// would leave CUs idle, also with a few more images in the same launch: up to
+// 320 at scale 2 (48 x 32; 512^2 HR 54.4 -> 38.7 us a pass, 666^2 54.5 -> 45.3,
+// ten of 512^2 147 -> 143, but 1024^2 57.7 -> 61.6), up to 128 at the other
+// scales, whose narrow tile does a quarter more work per pixel (scale 3: 576^2
+// and smaller 66 -> 55 us a pass, ten of 510^2 98 -> 104).  The rule takes the
+// geometry alone, so that a solve has the same tiles by itself, in a batch and
+// served.
+bool misr::use_narrow(int S, int Lp, int H, int W) {
+    const int th = tile_hr(S, Lp), tw = tile_wr(S, Lp | (kNarrow << 8));
+    if (th <= 0 || tw <= 0 || tw >= tile_wr(S, Lp)) return false;
+    const long long n = (long long)((H + th - 1) / th) * ((W + tw - 1) / tw);
+    return n <= (S == 2 ? 320 : 128);
+}
+
+// Sets the operator's tiles: variant tv, or (nar) variant 0's kernels on
+// narrow tiles.
+static void set_tile_variant(misr_op *op, int tv, bool nar) {
+    op->tv = tv;
+    op->nar = nar;
+    const int key = nar ? op->Lp | (kNarrow << 8) : op->kernel_key();
+    op->TH = tile_hr(op->s, key);
+    op->TW = tile_wr(op->s, key);
+    op->TWt = nar ? op->TW : tile_wt(op->s, key);
+}
+
 extern "C" misr_status misr_op_create(misr_ctx *ctx, const misr_geometry *g, misr_op **out) {
     if (!ctx || !out) return set_error(MISR_E_INVAL, "ctx/out is NULL");
     *out = nullptr;
@@ -635,9 +661,7 @@ extern "C" misr_status misr_op_create(misr_ctx *ctx, const misr_geometry *g, mis
     }
     op->L = band_length(g);
     op->Lp = padded_band(op->s, op->L);
-    op->TH = tile_hr(op->s, op->Lp);
-    op->TW = tile_wr(op->s, op->Lp);
-    op->TWt = tile_wt(op->s, op->Lp);
+    set_tile_variant(op.get(), 0, use_narrow(op->s, op->Lp, op->H, op->W));
     op->shifts.assign(g->shifts_lr, g->shifts_lr + 2 * g->n_frames);
     // taps per frame and axis: [K][2][P], vertical then horizontal
     if (g->psf_frames) {
@@ -818,12 +842,13 @@ hipError_t misr::ensure_tiles(const misr_op *op, const misr_params &p, TileSet &
 // few tile columns, so that those neighbours are a few items apart and their
 // rows still in the XCD's L2, instead of a whole tile row apart (the windows
 // of the 64 tiles of a 6144-px row fill an XCD's 4 MB L2).
-static void add_items(std::vector<Item> &items, int pj, int rows, int cols, int TH, int TW) {
+static void add_items(std::vector<Item> &items, int pj, int rows, int cols, int TH, int TW,
+                      bool nar) {
     const int nty = (rows + TH - 1) / TH, ntx = (cols + TW - 1) / TW;
     for (int i = 0; i < nty * ntx; ++i) {
         int ty, tx;
         strip_tile(i, nty, ntx, ty, tx);
-        items.push_back(Item{pj, ty, tx, 0});
+        items.push_back(Item{pj, ty, tx, nar ? 1 : 0});
     }
 }
 
@@ -883,8 +908,8 @@ void misr::add_views(const misr_op *op, const misr_params &prm, const void *y, v
         P.ntx = (op->W + op->TW - 1) / op->TW;
         const int pj = (int)projs.size();
         projs.push_back(P);
-        add_items(items, pj, op->H, op->W, op->TH, op->TWt);
-        add_items(items_u, pj, op->H, op->W, op->TH, op->TW);
+        add_items(items, pj, op->H, op->W, op->TH, op->TWt, op->nar);
+        add_items(items_u, pj, op->H, op->W, op->TH, op->TW, op->nar);
         return;
     }
     const TileGrid g = tile_grid(op, prm);
@@ -919,8 +944,8 @@ void misr::add_views(const misr_op *op, const misr_params &prm, const void *y, v
             Q.ntx = (C1 - C0 + op->TW - 1) / op->TW;
             const int pj = (int)projs.size();
             projs.push_back(Q);
-            add_items(items, pj, R1 - R0, C1 - C0, op->TH, op->TWt);
-            add_items(items_u, pj, Q.Hb, Q.Wb, op->TH, op->TW);
+            add_items(items, pj, R1 - R0, C1 - C0, op->TH, op->TWt, op->nar);
+            add_items(items_u, pj, Q.Hb, Q.Wb, op->TH, op->TW, op->nar);
         }
     // halo exchanges: every view's halo from the views that own it
     const int v1 = (int)projs.size();
@@ -1473,13 +1498,6 @@ extern "C" misr_status misr_time_pass(const misr_op *cop, const misr_params *prm
 }
 
 // ------------------------------------------------------------ tile autotuner
-static void set_tile_variant(misr_op *op, int tv) {
-    op->tv = tv;
-    op->TH = tile_hr(op->s, op->kernel_key());
-    op->TW = tile_wr(op->s, op->kernel_key());
-    op->TWt = tile_wt(op->s, op->kernel_key());
-}
-
 extern "C" misr_status misr_op_tune(misr_op *op, const misr_params *prm, const void *y, void *x,
                                     int reps, int32_t *tile_h, int32_t *tile_w, void *stream) {
     if (!op || !y || !x || !tile_h || !tile_w || reps < 1)
@@ -1492,30 +1510,36 @@ extern "C" misr_status misr_op_tune(misr_op *op, const misr_params *prm, const v
     std::lock_guard<std::mutex> lc(op->ctx->mu);
     MISR_HIP(set_device(op->ctx->dev));
     if (!op->general) {
-        const int prev = op->tv;   // kept if a timing run fails
+        // kept if a timing run fails
+        const int prev = op->tv;
+        const bool prev_nar = op->nar;
+        const bool can_nar = use_narrow(op->s, op->Lp, op->H, op->W);
         double best = 0.0;
-        int best_tv = 0;
-        for (int tv = 0; tv < 3; ++tv) {
-            if (tile_hr(op->s, op->Lp | (tv << 8)) <= 0) continue;
-            set_tile_variant(op, tv);
+        int best_tv = -1;
+        bool best_nar = false;
+        for (int c = 0; c < 4; ++c) {
+            // the three variants, then the narrow tiles of a small image
+            const int tv = c < 3 ? c : 0;
+            const bool nar = c == 3;
+            if (nar ? !can_nar : tile_hr(op->s, op->Lp | (tv << 8)) <= 0) continue;
+            set_tile_variant(op, tv, nar);
             // the two passes alternating, as in a solve: a trial tile that
             // lines up with the update tiles finds the update's output in its
             // XCD's L2, which timing each pass alone would not show
             double t_pair = 0.0;
             if ((st = time_pass_impl(op, prm, y, x, 2, reps, &t_pair, stream)) != MISR_OK) {
-                set_tile_variant(op, prev);
+                set_tile_variant(op, prev, prev_nar);
                 return st;
             }
-            if (tv == 0 || t_pair < best) {
+            if (best_tv < 0 || t_pair < best) {
                 best = t_pair;
                 best_tv = tv;
+                best_nar = nar;
             }
         }
-        set_tile_variant(op, best_tv);
+        set_tile_variant(op, best_tv, best_nar);
     }
-    *tile_h = op->TH;
-    *tile_w = op->TW;
-    return MISR_OK;
+    return misr_op_tile(op, tile_h, tile_w);
 }
 
 extern "C" misr_status misr_op_set_tile(misr_op *op, int variant) {
@@ -1524,14 +1548,15 @@ extern "C" misr_status misr_op_set_tile(misr_op *op, int variant) {
     if (variant < 0 || variant > 2 || tile_hr(op->s, op->Lp | (variant << 8)) <= 0)
         return set_error(MISR_E_INVAL, "tile variant %d not compiled", variant);
     std::lock_guard<std::mutex> lk(op->mu);
-    set_tile_variant(op, variant);
+    set_tile_variant(op, variant, false);
     return MISR_OK;
 }
 
 extern "C" misr_status misr_op_tile(const misr_op *op, int32_t *tile_h, int32_t *tile_w) {
     if (!op || !tile_h || !tile_w) return set_error(MISR_E_INVAL, "NULL argument");
-    *tile_h = op->TH;
-    *tile_w = op->TW;
+    // the variant's shape, also while a small image runs the narrow tiles
+    *tile_h = op->general ? 0 : tile_hr(op->s, op->kernel_key());
+    *tile_w = op->general ? 0 : tile_wr(op->s, op->kernel_key());
     return MISR_OK;
 }
 
@@ -1539,6 +1564,6 @@ extern "C" misr_status misr_op_tile_variant(const misr_op *op, int32_t *variant,
                                             int32_t *trial_w) {
     if (!op || !variant || !trial_w) return set_error(MISR_E_INVAL, "NULL argument");
     *variant = op->general ? -1 : op->tv;
-    *trial_w = op->TWt;
+    *trial_w = op->general ? 0 : tile_wt(op->s, op->kernel_key());
     return MISR_OK;
 }

@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "device_common.h"
 
@@ -45,7 +46,8 @@ constexpr int kNWI = kNTI / 64;    // waves per workgroup
 // in both the trial and the update pass; variant 1 is about half as wide;
 // variant 2 is a trial-kernel shape as wide as the trial pass's LDS alone
 // allows (the update pass stages two windows), paired with variant 0's
-// update shape.
+// update shape; kNarrow is the narrow tile that variant 0's kernels run for
+// small images.
 constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 constexpr int odd(int v) { return (v % 2) ? v : v + 1; }
 
@@ -98,11 +100,12 @@ struct Tile {
         int best = kNWI * S;
         for (int tw = kNWI * S; tw <= 1024; tw += kNWI * S)
             if ((tw + L - 2) / S + 1 <= 64 && shape_floats(tw) * 4 <= 79 * 1024) best = tw;
-        // variant 1: about half as wide (more workgroups for small images)
-        if (TV == 1) {
-            const int half = best / 2 / (kNWI * S) * (kNWI * S);
-            best = half > kNWI * S ? half : kNWI * S;
-        }
+        // variant 1: about half as wide (more workgroups for small images);
+        // the narrow tile: two columns per wave and phase at scale 2, else as
+        // variant 1
+        const int half = best / 2 / (kNWI * S) * (kNWI * S);
+        if (TV == 1 || TV == kNarrow) best = half > kNWI * S ? half : kNWI * S;
+        if (TV == kNarrow && S == 2) best = 2 * kNWI * S;
         return best;
     }
     static constexpr int TW = calc_tw();
@@ -376,14 +379,26 @@ __device__ constexpr int kDY[8] = {0, 0, 1, 1, 1, 2, 2, 2};
 // slots, so the loop is unrolled by three and nothing is moved.  Steps 0
 // and 1 (columns cv0-2, cv0-1) only fill the history.  The gradient
 // accumulates into gs (LDS, row stride GP).
+//
+// Rounding of a pixel's sums: the shares gamma_d psi(z_d) = g z are rounded
+// products, except that in interior tiles (CHECK = false) a share that enters
+// a single sum of its wave's strip is fused into it: the shares from the two
+// columns before the strip (first column), and the shares whose partner lies
+// past the strip (last one or two columns).  The narrow tile rounds as the
+// wide one does, so that results do not depend on which of them a pixel falls
+// into: cw0 is the strip's first column within the strips of variant 0.
 template <int S, int L, int TV, bool EPS0, bool CHECK>
 FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, int U0, int V0,
-                  int H, int W, int th_own, int tw_own, double &e_reg) {
+                  int H, int W, int th_own, int tw_own, int cw0, double &e_reg) {
+#pragma clang fp contract(off)
     using T = Tile<S, L, TV>;
-    constexpr int NSTEP = T::CV + 2;
+    constexpr bool NAR = TV == kNarrow;
+    constexpr int CV = T::CV, NSTEP = CV + 2;
+    // the strips whose edges fix the rounding: CVW columns, the last FL fused
+    constexpr int CVW = NAR ? Tile<S, L, 0>::CV : CV, FL = (CVW + 2) % 3;
     const int lane = threadIdx.x & 63, wv = uni(threadIdx.x >> 6);
     const int u = lane - 2;
-    const int cv0 = wv * T::CV;
+    const int cv0 = wv * CV;
     const int U = U0 + u;
     const int ur = min(u, T::TH - 1);
     const float e2 = eps * eps;
@@ -397,6 +412,7 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
     float *grow = gs + max(u, 0) * T::GP + cv0 - 2;
     float win[3][3];    // win[dy][slot]: window column c (from cv0 - 2) sits in slot (c + 1) % 3
     float hist[3][8];   // hist[slot][d]: the step's lambda gamma_d psi(z_d), slot t % 3
+    float hz[3][8], hg[3][8];   // its factors
 #pragma unroll
     for (int dy = 0; dy < 3; ++dy) {
         win[dy][1] = base[dy * T::WCP + 0];
@@ -410,8 +426,11 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
 #pragma unroll
     for (int d = 0; d < 8; ++d) gam_sum += gam[d];
     double eacc = 0.0;
-    // step t handles column cv0 + t - 2 and loads window column t + 2 (slot t % 3)
-    auto step = [&](auto slot_c, auto out_c, int t) {
+    // step t handles column cv0 + t - 2 and loads window column t + 2 (slot
+    // t % 3); FIRST: fused shares from the columns before, LAST: shares with
+    // dx >= LAST fused into the pixel's own sum
+    auto step = [&](auto slot_c, auto out_c, int t, auto kind) {
+#pragma clang fp contract(off)
         constexpr int Q = decltype(slot_c)::value;
         constexpr bool OUT = decltype(out_c)::value;
 #pragma unroll
@@ -444,6 +463,8 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
                 const float dd = fmaf(z, z, e2);
                 const float gr = gam[d] * rsq(dd);
                 hist[Q][d] = gr * z;
+                hz[Q][d] = z;
+                hg[Q][d] = gr;
                 eb = fmaf(gr, dd, eb);
             }
         }
@@ -451,12 +472,20 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
         if (OUT) {
             // shares of the pairs (i - d, i): from dx steps back, dy lanes up
             float own = 0.f, back[3] = {0.f, 0.f, 0.f};
+            auto sums = [&](auto first_c, auto last_c) {
+#pragma clang fp contract(off)
+                constexpr bool FIRST = decltype(first_c)::value && !CHECK && !EPS0;
+                constexpr int LAST = CHECK || EPS0 ? 3 : decltype(last_c)::value;
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                const int dx = kDX[d], dy = kDY[d];
-                own += hist[Q][d];
-                back[dy] += hist[(Q + 3 - dx) % 3][d];
-            }
+                for (int d = 0; d < 8; ++d) {
+                    const int dx = kDX[d], dy = kDY[d];
+                    own = dx >= LAST ? fmaf(hz[Q][d], hg[Q][d], own) : own + hist[Q][d];
+                    const int P = (Q + 3 - dx) % 3;
+                    back[dy] = FIRST && dx > 0 ? fmaf(hz[P][d], hg[P][d], back[dy])
+                                               : back[dy] + hist[P][d];
+                }
+            };
+            kind(sums);
             const float up = wave_shr1(back[1] + wave_shr1(back[2]));
             const float gsum = own - back[0] - up;
             if (row_tile) grow[t] += gsum;
@@ -466,20 +495,48 @@ FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, 
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
     using F = std::false_type;
     using Tr = std::true_type;
-    step(I0{}, F{}, 0);
-    step(I1{}, F{}, 1);
-    step(I2{}, Tr{}, 2);
+    auto mid = [](auto sums) { sums(F{}, I3{}); };
+    step(I0{}, F{}, 0, mid);
+    step(I1{}, F{}, 1, mid);
+    if constexpr (NAR) {
+        // strips that start and end with variant 0's, or anywhere in them
+        constexpr bool ALIGNED = CVW % CV == 0;
+        auto at = [&](auto c_c) {
+            constexpr int c = decltype(c_c)::value;
+            step(std::integral_constant<int, (c + 2) % 3>{}, Tr{}, c + 2, [&](auto sums) {
+                const int cw = cw0 + c >= CVW ? cw0 + c - CVW : cw0 + c;   // uniform
+                constexpr bool HEAD = !ALIGNED || c == 0, TAIL = !ALIGNED || c >= CV - 2;
+                if (HEAD && cw == 0)
+                    sums(Tr{}, I3{});
+                else if (TAIL && FL == 2 && cw == CVW - 2)
+                    sums(F{}, I2{});
+                else if (TAIL && FL >= 1 && cw == CVW - 1)
+                    sums(F{}, I1{});
+                else
+                    sums(F{}, I3{});
+            });
+        };
+        [&]<int... c>(std::integer_sequence<int, c...>) {
+            (at(std::integral_constant<int, c>{}), ...);
+        }(std::make_integer_sequence<int, CV>{});
+    } else {
+        step(I2{}, Tr{}, 2, [](auto sums) { sums(Tr{}, I3{}); });
 #pragma unroll 1
-    for (int t = 3; t + 2 < NSTEP; t += 3) {
-        step(I0{}, Tr{}, t);
-        step(I1{}, Tr{}, t + 1);
-        step(I2{}, Tr{}, t + 2);
+        for (int t = 3; t + 2 < NSTEP; t += 3) {
+            step(I0{}, Tr{}, t, mid);
+            step(I1{}, Tr{}, t + 1, mid);
+            step(I2{}, Tr{}, t + 2, mid);
+        }
+        // steps after the last full group of three
+        if constexpr (FL == 1) step(I0{}, Tr{}, NSTEP - 1, [](auto sums) { sums(F{}, I1{}); });
+        if constexpr (FL == 2) {
+            step(I0{}, Tr{}, NSTEP - 2, [](auto sums) { sums(F{}, I2{}); });
+            step(I1{}, Tr{}, NSTEP - 1, [](auto sums) { sums(F{}, I1{}); });
+        }
     }
-    constexpr int REM = NSTEP % 3;   // steps after the last full group of three
-    if constexpr (REM >= 1) step(I0{}, Tr{}, NSTEP - REM);
-    if constexpr (REM >= 2) step(I1{}, Tr{}, NSTEP - REM + 1);
     e_reg += eacc;
 }
 
@@ -817,7 +874,7 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
     // g_k at the owned pixels; the wide tile issues these loads before the
     // prior's sweep so that they are in flight during it, the narrow tile
     // (whose sweep leaves no registers to carry them) after it
-    constexpr bool PRE = TV == 0;
+    constexpr bool PRE = TV == 0 || TV == kNarrow;
     float gkv[ONR][ONC];
     auto load_gk = [&]() {
         __builtin_amdgcn_s_setprio(2);
@@ -835,16 +892,23 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
     for (int d = 0; d < 8; ++d) gam[d] = st.wt.gam[kDY[d] * 3 + kDX[d]];
     const float eps = st.wt.eps;
     double e_reg = 0.0;
-    // interior tiles: every pair of the sweep lies inside the image, tile owned whole
-    const bool inner = o.U0 >= 2 && o.V0 >= 2 && o.U0 + T::TH + 2 <= H &&
-                       o.V0 + T::TW + 2 <= W && o.u1 - o.u0 == T::TH && o.v1 - o.v0 == T::TW;
+    // interior tiles: every pair of the sweep lies inside the image, tile owned
+    // whole; a narrow tile goes by the wide tile it lies in
+    constexpr int TWW = TV == kNarrow ? Tile<S, L, 0>::TW : T::TW;
+    const int vrel = o.v0 - P.ox0, vin = vrel % TWW;
+    const bool inner = o.U0 >= 2 && o.V0 - vin >= 2 && o.U0 + T::TH + 2 <= H &&
+                       o.V0 - vin + TWW + 2 <= W && o.u1 - o.u0 == T::TH &&
+                       o.v0 - vin + TWW <= P.ox1;
     const int tho = o.u1 - o.u0, two = o.v1 - o.v0;
+    const int cw0 = (vin + wv0 * T::CV) % (TWW / kNWI);
     if (eps == 0.f)
-        btv_sweep<S, L, TV, true, true>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, e_reg);
+        btv_sweep<S, L, TV, true, true>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, cw0, e_reg);
     else if (inner)
-        btv_sweep<S, L, TV, false, false>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, e_reg);
+        btv_sweep<S, L, TV, false, false>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, cw0,
+                                          e_reg);
     else
-        btv_sweep<S, L, TV, false, true>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, e_reg);
+        btv_sweep<S, L, TV, false, true>(xs, gs, gam, eps, o.U0, o.V0, H, W, tho, two, cw0,
+                                         e_reg);
     __syncthreads();
     // owned gradient out, with its inner products (g_k is widened to double
     // only here: widened at its load, it would be carried across the sweep
@@ -1193,6 +1257,14 @@ FI void tile_adjoint(const AS4 Proj &P, int ty, int tx, const void *r, float *xo
 // item xcd_item(b, n): XCD b % 8 gets one contiguous run of the list (a band
 // of neighbouring tiles), so the halos neighbouring tiles share are re-read
 // from that XCD's L2 rather than fetched again.
+//
+// A tile is a chain of dependent phases (windows in, a barrier per frame, the
+// sweeps, the reduction): a 48 x 96 tile alone on a CU takes 22 us at scale 2
+// whatever the image, so an image of few tiles leaves most CUs idle for as
+// long.  Items of small images (Item::nar) are narrow tiles of the same
+// height: 48 x 32 takes 15 us (trial) and 11-13 us (update; 48 x 96: 20-27).
+// The same kernels run them, so that a batch of small and large images stays
+// one launch per pass.
 FI int xcd_item(int b, int n) {
     const int q = n >> 3, r = n & 7, x = b & 7, j = b >> 3;
     return x * q + min(x, r) + j;
@@ -1213,7 +1285,12 @@ __global__ void __launch_bounds__(kNTI, 4) k_trial(const Proj *projs, const Item
     const AS4 Proj &P = cst(projs)[itm.proj];
     const AS4 ScgState &st = *cst(P.st);
     if (mode == 1 && !st.active) return;
-    tile_trial<S, L, TV, ST, SY>(P, st, itm.ty, itm.tx, mode, sm, red, partials + (i64)it * kNV);
+    double *part = partials + (i64)it * kNV;
+    if (TV == 0 && itm.nar)
+        tile_trial<S, L, TV == 0 ? kNarrow : TV, ST, SY>(P, st, itm.ty, itm.tx, mode, sm,
+                                                                red, part);
+    else
+        tile_trial<S, L, TV, ST, SY>(P, st, itm.ty, itm.tx, mode, sm, red, part);
 }
 
 template <int S, int L, int TV, class ST, class SY>
@@ -1229,7 +1306,12 @@ __global__ void __launch_bounds__(kNTI, 4) k_upcurv(const Proj *projs, const Ite
     const AS4 Proj &P = cst(projs)[itm.proj];
     const AS4 ScgState &st = *cst(P.st);
     if (!st.do_update) return;
-    tile_upcurv<S, L, TV, ST, SY>(P, st, itm.ty, itm.tx, sm, red, partials + (i64)it * kNV);
+    double *part = partials + (i64)it * kNV;
+    if (TV == 0 && itm.nar)
+        tile_upcurv<S, L, TV == 0 ? kNarrow : TV, ST, SY>(P, st, itm.ty, itm.tx, sm, red,
+                                                                 part);
+    else
+        tile_upcurv<S, L, TV, ST, SY>(P, st, itm.ty, itm.tx, sm, red, part);
 }
 
 template <int S, int L, int TV, class ST>
@@ -1238,7 +1320,11 @@ __global__ void __launch_bounds__(kNTI) k_forward(const Proj *projs, const Item 
     __shared__ float sm[Tile<S, L, TV>::SMEM_F];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const AS4 Item &itm = cst(items)[it];
-        tile_forward<S, L, TV, ST>(cst(projs)[itm.proj], itm.ty, itm.tx, yout, sm);
+        const AS4 Proj &P = cst(projs)[itm.proj];
+        if (TV == 0 && itm.nar)
+            tile_forward<S, L, TV == 0 ? kNarrow : TV, ST>(P, itm.ty, itm.tx, yout, sm);
+        else
+            tile_forward<S, L, TV, ST>(P, itm.ty, itm.tx, yout, sm);
         __syncthreads();
     }
 }
@@ -1249,7 +1335,11 @@ __global__ void __launch_bounds__(kNTI) k_adjoint(const Proj *projs, const Item 
     __shared__ float sm[Tile<S, L, TV>::SMEM_A];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const AS4 Item &itm = cst(items)[it];
-        tile_adjoint<S, L, TV, ST>(cst(projs)[itm.proj], itm.ty, itm.tx, r, xout, sm);
+        const AS4 Proj &P = cst(projs)[itm.proj];
+        if (TV == 0 && itm.nar)
+            tile_adjoint<S, L, TV == 0 ? kNarrow : TV, ST>(P, itm.ty, itm.tx, r, xout, sm);
+        else
+            tile_adjoint<S, L, TV, ST>(P, itm.ty, itm.tx, r, xout, sm);
         __syncthreads();
     }
 }
@@ -1295,7 +1385,8 @@ __global__ void __launch_bounds__(kNTI) k_adjoint(const Proj *projs, const Item 
         BODY                          \
     }
 
-// Tile shapes of a kernel key (band length | variant << 8): the update
+// Tile shapes of a kernel key (band length | variant << 8, or | kNarrow << 8
+// for the narrow tile of variant 0's kernels): the update
 // pass's (and the operators'), then the trial pass's.  Variant 2 pairs the
 // trial kernel's own wider shape with variant 0's update shape; it exists
 // only where that shape is wider.
@@ -1308,6 +1399,16 @@ int MISR_FN(tile_dims_s)(int key, int *th, int *tw) {
     const int v = key >> 8, Lp = key & 255;
 #define X(l)                                                        \
     if (Lp == l) {                                                  \
+        if (v == kNarrow) {                                         \
+            using TN = Tile<MISR_SCALE, l, kNarrow>;            \
+            using T0 = Tile<MISR_SCALE, l, 0>;                      \
+            static_assert(TN::SMEM <= T0::SMEM && TN::SMEM_U <= T0::SMEM_U && \
+                          TN::SMEM_F <= T0::SMEM_F && TN::SMEM_A <= T0::SMEM_A, \
+                          "narrow tiles run in variant 0's kernels"); \
+            *th = TN::TH;                                           \
+            *tw = TN::TW;                                           \
+            return 1;                                               \
+        }                                                           \
         if (v == 1) {                                               \
             *th = Tile<MISR_SCALE, l, 1>::TH;                       \
             *tw = Tile<MISR_SCALE, l, 1>::TW;                       \

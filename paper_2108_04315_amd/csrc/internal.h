@@ -13,6 +13,9 @@ constexpr int kMaxK = 16;    // frames per projection
 constexpr int kMaxL = 16;    // band length
 constexpr int kPadRows = 16; // zero weight rows before each frame's table
 
+// Shape key of the narrow tile (tile_hr, tile_wr).
+constexpr int kNarrow = 3;
+
 enum StorageType : int { ST_F32 = 0, ST_F16 = 1, ST_BF16 = 2, ST_U16 = 3 };
 // Launch code of the image kernels: storage of the views' iterate x (low
 // nibble) and of the frames y (high nibble).
@@ -148,7 +151,7 @@ __host__ __device__ inline void strip_tile(int i, int nty, int ntx, int &ty, int
 struct Item {
     int proj;            // index into Proj array
     int ty, tx;          // tile coordinates in the owned rectangle
-    int pad_;
+    int nar;             // 1: a narrow tile (small images) of the class
 };
 
 // Objective weights for the kernels (float) plus solver constants.

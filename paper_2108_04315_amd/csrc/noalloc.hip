@@ -55,8 +55,8 @@ Layout layout(long long n_items) {
 // Writes the solver state (objective weights), the view (pointing at that
 // state) and the item list of one untiled image into the workspace: item i
 // is tile strip_tile(i), the order of the library's own work lists.
-__global__ void k_noalloc_setup(Proj P, ScgState S, int nty, int ntx, unsigned char *base,
-                                Layout l) {
+__global__ void k_noalloc_setup(Proj P, ScgState S, int nty, int ntx, int nar,
+                                unsigned char *base, Layout l) {
     const int n = nty * ntx;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) {
@@ -69,7 +69,7 @@ __global__ void k_noalloc_setup(Proj P, ScgState S, int nty, int ntx, unsigned c
     if (i < n) {
         int ty, tx;
         strip_tile(i, nty, ntx, ty, tx);
-        ((Item *)(base + l.items))[i] = Item{0, ty, tx, 0};
+        ((Item *)(base + l.items))[i] = Item{0, ty, tx, nar};
     }
 }
 
@@ -145,7 +145,8 @@ extern "C" misr_status misr_cost_grad_noalloc(const misr_op *op, const misr_para
     hipStream_t s = (hipStream_t)stream;
     unsigned char *b = (unsigned char *)base;
     const int blocks = (int)((n_items + 255) / 256);
-    hipLaunchKernelGGL(k_noalloc_setup, dim3(blocks), dim3(256), 0, s, P, S, nty, ntx, b, l);
+    hipLaunchKernelGGL(k_noalloc_setup, dim3(blocks), dim3(256), 0, s, P, S, nty, ntx,
+                       op->nar ? 1 : 0, b, l);
     MISR_HIP(hipGetLastError());
     MISR_HIP(launch_image(op->s, op->kernel_key(), (int)n_items, s, (const Proj *)(b + l.proj),
                           (const Item *)(b + l.items), (const int *)(b + l.cnt),

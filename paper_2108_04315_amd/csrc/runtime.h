@@ -265,6 +265,8 @@ struct misr_op {
     misr_ctx *ctx;
     int H, W, s, K, P, L, Lp, TH, TW;  // TH x TW: HR tile of the image kernels
     int TWt = 0;                       // TH x TWt: the trial kernel's tile
+    bool nar = false;                  // runs the narrow tiles (TW = TWt = their width);
+                                       // tv, as reported, stays 0
     int tv = 0;                        // tile variant (set by misr_op_tune)
     // key of the image kernels: band length and tile variant
     int kernel_key() const { return Lp | (tv << 8); }
@@ -292,6 +294,8 @@ namespace misr {
 
 // SCG state of a new solve from its parameters (N = HR pixels).
 void init_state(ScgState &s, const misr_params &p, long long N);
+// Whether an untuned operator of this geometry runs the narrow tiles.
+bool use_narrow(int S, int Lp, int H, int W);
 // Looks up, on device dev (current), the address of the workspace of
 // misr_cost_grad_noalloc; once per device (noalloc.hip).
 hipError_t scratch_init(int dev);

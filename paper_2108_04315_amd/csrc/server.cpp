@@ -224,8 +224,8 @@ static size_t request_bytes(const misr_request &q, long long n, size_t es, int K
 
 // Device bytes of a request's share of the work lists: its trial and update
 // items (an Item and kNV FP64 partial sums each), views and halo copies, in
-// each of the two alternating cycles' lists.  Server operators keep tile
-// variant 0.
+// each of the two alternating cycles' lists.  Server operators keep the
+// untuned tiles.
 static size_t list_bytes(const misr_request &q, bool general) {
     const int H = q.geom.hr_h, W = q.geom.hr_w, s = q.geom.scale, K = q.geom.n_frames;
     long long ni = 0, nu = 0, nviews = 1, nhalo = 0;
@@ -237,7 +237,9 @@ static size_t list_bytes(const misr_request &q, bool general) {
                             cd((long long)H * W, kGenRows);
     } else {
         const int Lp = padded_band(s, band_length(&q.geom));
-        const int TH = tile_hr(s, Lp), TW = tile_wr(s, Lp), TWt = tile_wt(s, Lp);
+        const bool nar = Lp > 0 && use_narrow(s, Lp, H, W);
+        const int TH = tile_hr(s, Lp), TW = tile_wr(s, nar ? Lp | (kNarrow << 8) : Lp);
+        const int TWt = nar ? TW : tile_wt(s, Lp);
         if (TH <= 0 || TW <= 0 || TWt <= 0) return 0;   // rejected at op creation
         if (q.params.tile_lr <= 0) {
             ni = cd(H, TH) * cd(W, TWt);
