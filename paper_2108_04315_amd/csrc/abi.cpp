@@ -57,20 +57,48 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
     for (size_t i = 0; i < ns; ++i)
         pl.refs[i] = SolveRef{sd + i, per ? traces.as<IterRec>() + i * per : nullptr,
                               pl.item0[i], pl.nitems[i], pl.item0u[i], pl.nitemsu[i]};
+    // A call uploads the arrays whose bytes differ from what the device holds.
+    // A repeated call on an operator differs in the views (its buffers) and,
+    // after a solve, in the states: short arrays, which go with one launch
+    // (launch_put).  Seven copies from pageable memory cost a call about 20 us
+    // of host time before.
     struct Up {
-        void *d;
+        DevMem &d;
         const void *h;
         size_t n;
-    } ups[] = {{projs.p, pl.projs.data(), np * sizeof(Proj)},
-               {items.p, pl.items.data(), ni * sizeof(Item)},
-               {items_u.p, pl.items_u.data(), nu * sizeof(Item)},
-               {counts.p, pl.counts.data(), pl.counts.size() * sizeof(int)},
-               {refs.p, pl.refs.data(), ns * sizeof(SolveRef)},
-               {halos.p, pl.halos.data(), nh * sizeof(HaloCopy)},
-               {states.p, pl.states.data(), ns * sizeof(ScgState)}};
-    for (auto &u : ups)
-        if (u.n && (e = hipMemcpyAsync(u.d, u.h, u.n, hipMemcpyHostToDevice, stream)) != hipSuccess)
-            return e;
+    } ups[] = {{projs, pl.projs.data(), np * sizeof(Proj)},
+               {items, pl.items.data(), ni * sizeof(Item)},
+               {items_u, pl.items_u.data(), nu * sizeof(Item)},
+               {counts, pl.counts.data(), pl.counts.size() * sizeof(int)},
+               {refs, pl.refs.data(), ns * sizeof(SolveRef)},
+               {halos, pl.halos.data(), nh * sizeof(HaloCopy)},
+               {states, pl.states.data(), ns * sizeof(ScgState)}};
+    constexpr int kStates = 6;
+    if (states_dirty) held[kStates].p = nullptr;
+    PutArgs put;
+    put.n = 0;
+    size_t at = 0;   // bytes in put
+    for (int i = 0; i < 7; ++i) {
+        Up &u = ups[i];
+        Held &hd = held[i];
+        if (!u.n || (hd.p == u.d.p && hd.b.size() == u.n && !std::memcmp(hd.b.data(), u.h, u.n)))
+            continue;
+        hd.p = nullptr;   // (not held while the upload may fail)
+        if (at + u.n <= kPutBytes && u.n % 4 == 0) {
+            put.dst[put.n] = u.d.as<unsigned>();
+            put.words[put.n++] = (int)(u.n / 4);
+            std::memcpy((unsigned char *)put.w + at, u.h, u.n);
+            at += u.n;
+        } else {
+            e = hipMemcpyAsync(u.d.p, u.h, u.n, hipMemcpyHostToDevice, stream);
+            if (e != hipSuccess) return e;
+        }
+        hd.b.assign((const unsigned char *)u.h, (const unsigned char *)u.h + u.n);
+    }
+    if (put.n && (e = launch_put(stream, put)) != hipSuccess) return e;
+    for (int i = 0; i < 7; ++i)
+        if (ups[i].n) held[i].p = ups[i].d.p;
+    states_dirty = false;
     return hipSuccess;
 }
 
@@ -1026,23 +1054,14 @@ static void build_plan(Plan &pl, const std::vector<SolveIn> &in) {
 }
 
 // Everything a captured solve bakes in as launch arguments: pass count,
-// storage codes, start-point kernels (kind, buffers, storage and grid with
-// the frames' integer offsets), counts and class ranges.
+// storage codes, counts and class ranges.  The caller's buffers are not among
+// them (the views hold those; the start-point kernels that take them directly
+// are launched before the graph), so a captured solve serves new frames.
 static std::string plan_key(const Plan &pl, int n_iter) {
     std::string k = std::to_string(n_iter) + "/" + std::to_string(pl.code()) + "," +
-                    std::to_string(pl.gt) + "/i";
-    for (auto &it : pl.inits) {
-        char b[96];
-        snprintf(b, sizeof b, "%d,%p,%p,%d,%d,%d,%d,%d", it.kind, it.y, it.x, it.st, it.a.H,
-                 it.a.W, it.a.s, it.a.K);
-        k += b;
-        for (int f = 0; f < it.a.K; ++f)
-            k += "," + std::to_string(it.a.ty[f]) + "," + std::to_string(it.a.tx[f]);
-        k += ";";
-    }
-    k += "/" +
-                     std::to_string(pl.states.size()) + "/" + std::to_string(pl.projs.size()) +
-                     "/" + std::to_string(pl.halos.size()) + (pl.staged ? "S" : "U");
+                    std::to_string(pl.gt) + "/" + std::to_string(pl.states.size()) + "/" +
+                    std::to_string(pl.projs.size()) + "/" + std::to_string(pl.halos.size()) +
+                    (pl.staged ? "S" : "U");
     for (auto &c : pl.classes)
         k += ":" + std::to_string(c.S) + "," + std::to_string(c.Lp) + "," +
              std::to_string(c.start) + "," + std::to_string(c.count);
@@ -1089,14 +1108,15 @@ struct Launcher {
     }
 };
 
-// Enqueues the whole solve (init + n_iter passes + result copy) on `s`.
-static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, hipStream_t s) {
+// Enqueues the whole solve (init + n_iter passes + result copy) on `s`; last:
+// where the final state of a single solve is kept, or NULL.
+static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, ScgState *last,
+                                hipStream_t s) {
     const Launcher Lr{pl, pd, s};
     const int np = (int)pl.projs.size();
     hipError_t e = hipSuccess;
 #define STEP(x)                          \
     if ((e = (x)) != hipSuccess) return e;
-    for (auto &it : pl.inits) STEP(launch_init(s, it.kind, it.a, it.y, it.x, it.st));
     if (pl.staged) STEP(launch_scatter(s, pd.projs.as<Proj>(), np, pl.vt, pl.gt));
     STEP(Lr.image(KIND_COSTGRAD));
     STEP(Lr.halo());
@@ -1109,6 +1129,7 @@ static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, hipStre
         STEP(Lr.scalar(PHASE_B));
         STEP(Lr.image(KIND_UPCURV));
     }
+    if (last) STEP(launch_copy_state(s, last, pd.states.as<ScgState>()));
 #undef STEP
     // staged views: owned parts back into the caller's image (rounded to its
     // storage); an unstaged view copies its workspace buffer back when the
@@ -1117,20 +1138,24 @@ static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, hipStre
                      : launch_finalize(s, pd.projs.as<Proj>(), np, pl.vt);
 }
 
-// Runs a plan on the context's library stream, ordered after the caller's
-// stream and before its later work; the solve is captured into a graph once
-// per plan shape and replayed.
-static misr_status run_plan(misr_ctx *ctx, Plan &pl, PlanDev &pd, int n_iter,
-                            hipStream_t user) {
-    hipStream_t s = ctx->stream;
-    MISR_HIP(hipEventRecord(ctx->ev_in, user));
-    MISR_HIP(hipStreamWaitEvent(s, ctx->ev_in, 0));
+// Runs a plan; the solve is captured into a graph (on the context's library
+// stream) once per plan shape and replayed.  A single solve replays on the
+// caller's stream: its workspace is the operator's, whose calls the caller
+// orders.  A batch, whose workspace all batches share, replays on the library
+// stream, ordered after the caller's stream and before its later work.
+static misr_status run_plan(misr_ctx *ctx, Plan &pl, PlanDev &pd, int n_iter, ScgState *last,
+                            bool shared, hipStream_t user) {
+    hipStream_t s = shared ? ctx->stream : user;
+    if (shared) {
+        MISR_HIP(hipEventRecord(ctx->ev_in, user));
+        MISR_HIP(hipStreamWaitEvent(s, ctx->ev_in, 0));
+    }
     MISR_HIP(pd.upload(pl, n_iter, s));
     // the graph bakes in the device addresses of the plan arrays
     char ptrs[256];
-    snprintf(ptrs, sizeof ptrs, "|%p,%p,%p,%p,%p,%p,%p,%p,%p", pd.projs.p, pd.items.p,
+    snprintf(ptrs, sizeof ptrs, "|%p,%p,%p,%p,%p,%p,%p,%p,%p,%p", pd.projs.p, pd.items.p,
              pd.items_u.p, pd.counts.p, pd.states.p, pd.partials.p, pd.partials_u.p, pd.refs.p,
-             pd.halos.p);
+             pd.halos.p, (void *)last);
     const std::string key = plan_key(pl, n_iter) + ptrs;
     if (!pd.exec || pd.graph_key != key) {
         if (pd.exec) {
@@ -1138,9 +1163,9 @@ static misr_status run_plan(misr_ctx *ctx, Plan &pl, PlanDev &pd, int n_iter,
             pd.exec = nullptr;
         }
         hipGraph_t graph = nullptr;
-        MISR_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        hipError_t e = enqueue_solve(pl, pd, n_iter, s);
-        hipError_t e2 = hipStreamEndCapture(s, &graph);
+        MISR_HIP(hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
+        hipError_t e = enqueue_solve(pl, pd, n_iter, last, ctx->stream);
+        hipError_t e2 = hipStreamEndCapture(ctx->stream, &graph);
         if (e != hipSuccess) {
             if (graph) (void)hipGraphDestroy(graph);
             return hip_fail(e, "enqueue_solve (capture)");
@@ -1154,9 +1179,13 @@ static misr_status run_plan(misr_ctx *ctx, Plan &pl, PlanDev &pd, int n_iter,
         }
         pd.graph_key = key;
     }
+    pd.states_dirty = true;   // from here on the kernels write them
+    for (auto &it : pl.inits) MISR_HIP(launch_init(s, it.kind, it.a, it.y, it.x, it.st));
     MISR_HIP(hipGraphLaunch(pd.exec, s));
-    MISR_HIP(hipEventRecord(ctx->ev_out, s));
-    MISR_HIP(hipStreamWaitEvent(user, ctx->ev_out, 0));
+    if (shared) {
+        MISR_HIP(hipEventRecord(ctx->ev_out, s));
+        MISR_HIP(hipStreamWaitEvent(user, ctx->ev_out, 0));
+    }
     return MISR_OK;
 }
 
@@ -1182,8 +1211,9 @@ static misr_status fetch_trace(PlanDev &pd, int idx, misr_scg_trace *tr, hipStre
 }
 
 // ------------------------------------------------------------ operators
-static void single_view(misr_op *op, const void *x, Plan &pl) {
-    SolveIn si{op, {}, nullptr, const_cast<void *>(x), &op->bufs, nullptr};
+// The plan of a standalone operator; its buffers go with the launch.
+static void single_view(misr_op *op, Plan &pl) {
+    SolveIn si{op, {}, nullptr, nullptr, &op->bufs, nullptr};
     misr_params_default(&si.prm);
     si.prm.n_iter = 0;
     build_plan(pl, {si});
@@ -1206,14 +1236,14 @@ extern "C" misr_status misr_forward(const misr_op *cop, misr_dtype dt, const voi
         return MISR_OK;
     }
     Plan &pl = op->plan;
-    single_view(op, x, pl);
+    single_view(op, pl);
     PlanDev &pd = op->pdev;
     hipStream_t s = (hipStream_t)stream;
     MISR_HIP(pd.upload(pl, 0, s));
     // the update list: tiles of the operator's (update-pass) shape
     MISR_HIP(launch_forward(op->s, op->kernel_key(), (int)pl.items_u.size(), s,
                             pd.projs.as<Proj>(), pd.items_u.as<Item>(), (int)pl.items_u.size(),
-                            (int)dt, y));
+                            (int)dt, x, y));
     return MISR_OK;
 }
 
@@ -1233,7 +1263,7 @@ extern "C" misr_status misr_adjoint(const misr_op *cop, misr_dtype dt, const voi
         return MISR_OK;
     }
     Plan &pl = op->plan;
-    single_view(op, x, pl);
+    single_view(op, pl);
     PlanDev &pd = op->pdev;
     hipStream_t s = (hipStream_t)stream;
     MISR_HIP(pd.upload(pl, 0, s));
@@ -1337,13 +1367,11 @@ extern "C" misr_status misr_scg_solve(const misr_op *cop, const misr_params *prm
     Plan &pl = op->plan;
     build_plan(pl, {SolveIn{op, *prm, y, x, &op->bufs, &op->tiles}});
     hipStream_t s = (hipStream_t)stream;
-    st = run_plan(op->ctx, pl, op->pdev, prm->n_iter, s);
-    if (st != MISR_OK) return st;
-    // the final state, kept for misr_scg_status (later calls on the op reuse
-    // the plan's state buffer)
+    // the final state goes to last_state, kept for misr_scg_status (later calls
+    // on the op reuse the plan's state buffer)
     MISR_HIP(op->last_state.ensure(sizeof(ScgState)));
-    MISR_HIP(hipMemcpyAsync(op->last_state.p, op->pdev.states.p, sizeof(ScgState),
-                            hipMemcpyDeviceToDevice, s));
+    st = run_plan(op->ctx, pl, op->pdev, prm->n_iter, op->last_state.as<ScgState>(), false, s);
+    if (st != MISR_OK) return st;
     op->have_last = true;
     if (trace) return fetch_trace(op->pdev, 0, trace, s);
     return MISR_OK;
@@ -1374,13 +1402,21 @@ extern "C" misr_status misr_scg_status(const misr_op *cop, misr_scg_trace *summa
 
 namespace {
 struct BatchCache {
-    std::vector<const misr_op *> ops;
+    misr_ctx *ctx = nullptr;
     std::vector<std::unique_ptr<SolveBufs>> bufs;
     PlanDev pdev;
     Plan plan;
 };
 std::mutex g_batch_mu;
 BatchCache *g_batch = nullptr;
+
+// Device bytes of one batch entry's buffers.
+size_t batch_bytes(const misr_op *op, const misr_params &p) {
+    const size_t n = (size_t)op->H * op->W;
+    size_t b = n * (view_esize(p) + 16 + (iterate_fp32(p) ? 4 : 0));
+    if (op->general) b += (size_t)kGenVecs * op->K * (op->H / op->s) * (op->W / op->s) * 4;
+    return b;
+}
 }  // namespace
 
 extern "C" misr_status misr_scg_solve_batch(int n, const misr_op *const *ops,
@@ -1405,13 +1441,25 @@ extern "C" misr_status misr_scg_solve_batch(int n, const misr_op *const *ops,
     std::lock_guard<std::mutex> lk(g_batch_mu);
     std::lock_guard<std::mutex> lc(ctx->mu);
     MISR_HIP(set_device(ctx->dev));
-    if (!g_batch) g_batch = new BatchCache();
-    BatchCache &bc = *g_batch;
-    std::vector<const misr_op *> key(ops, ops + n);
-    if (bc.ops != key) {
-        bc.bufs.clear();
-        bc.ops = key;
+    // one context's batches at a time (another's stream does not wait for
+    // this one's; freeing the buffers waits for the device)
+    if (g_batch && g_batch->ctx != ctx) {
+        delete g_batch;
+        g_batch = nullptr;
     }
+    if (!g_batch) {
+        g_batch = new BatchCache();
+        g_batch->ctx = ctx;
+    }
+    BatchCache &bc = *g_batch;
+    // Batches share one set of buffers per entry, grown as needed (a program
+    // that alternates between batches allocates nothing), and given back when
+    // they hold more than twice what the batch at hand needs.
+    size_t need = 0, have = 0;
+    for (int i = 0; i < n; ++i)
+        need += batch_bytes(ops[i], prm[i]);
+    for (auto &b : bc.bufs) have += b->bytes();
+    if (have > 2 * need) bc.bufs.clear();
     int n_iter = 0;
     for (int i = 0; i < n; ++i) n_iter = std::max(n_iter, prm[i].n_iter);
     std::vector<SolveIn> in;
@@ -1423,7 +1471,7 @@ extern "C" misr_status misr_scg_solve_batch(int n, const misr_op *const *ops,
     }
     build_plan(bc.plan, in);
     hipStream_t s = (hipStream_t)stream;
-    misr_status st = run_plan(ctx, bc.plan, bc.pdev, n_iter, s);
+    misr_status st = run_plan(ctx, bc.plan, bc.pdev, n_iter, nullptr, true, s);
     if (st != MISR_OK) return st;
     misr_status worst = MISR_OK;
     if (traces)
@@ -1452,6 +1500,7 @@ static misr_status time_pass_impl(misr_op *op, const misr_params *prm, const voi
     MISR_HIP(hipEventRecord(op->ctx->ev_in, (hipStream_t)stream));
     MISR_HIP(hipStreamWaitEvent(s, op->ctx->ev_in, 0));
     MISR_HIP(pd.upload(pl, 1, s));
+    pd.states_dirty = true;   // the scalar phases write them
     const Launcher Lr{pl, pd, s};
     MISR_HIP(Lr.image(KIND_COSTGRAD));
     MISR_HIP(Lr.scalar(PHASE_INIT));

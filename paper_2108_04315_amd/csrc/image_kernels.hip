@@ -1137,7 +1137,7 @@ FI void tile_upcurv(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, f
 
 // y[k] = A_k x on the owned LR pixels of one tile.
 template <int S, int L, int TV, class ST>
-FI void tile_forward(const AS4 Proj &P, int ty, int tx, void *yout, float *sm) {
+FI void tile_forward(const AS4 Proj &P, int ty, int tx, const void *xin, void *yout, float *sm) {
     using T = Tile<S, L, TV>;
     using raw = typename ST::raw;
     const AS4 OpDev &op = *cst(P.op);
@@ -1148,7 +1148,7 @@ FI void tile_forward(const AS4 Proj &P, int ty, int tx, void *yout, float *sm) {
     const TileOrigin o = tile_origin<S, L, TV>(P, ty, tx);
     const int h = op.H / S, w = op.W / S, K = op.K;
     float *xs = sm;
-    const AS1 raw *xb = glb((const raw *)P.x[0]);
+    const AS1 raw *xb = glb((const raw *)xin);
     const int Hb = P.Hb, Wb = P.Wb, ld = P.ld;
     for (int q = tid; q < T::WR * T::WC; q += kNTI) {
         const int r = q / T::WC, c = q - r * T::WC;
@@ -1316,15 +1316,15 @@ __global__ void __launch_bounds__(kNTI, 4) k_upcurv(const Proj *projs, const Ite
 
 template <int S, int L, int TV, class ST>
 __global__ void __launch_bounds__(kNTI) k_forward(const Proj *projs, const Item *items, int n,
-                                                  void *yout) {
+                                                  const void *xin, void *yout) {
     __shared__ float sm[Tile<S, L, TV>::SMEM_F];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const AS4 Item &itm = cst(items)[it];
         const AS4 Proj &P = cst(projs)[itm.proj];
         if (TV == 0 && itm.nar)
-            tile_forward<S, L, TV == 0 ? kNarrow : TV, ST>(P, itm.ty, itm.tx, yout, sm);
+            tile_forward<S, L, TV == 0 ? kNarrow : TV, ST>(P, itm.ty, itm.tx, xin, yout, sm);
         else
-            tile_forward<S, L, TV, ST>(P, itm.ty, itm.tx, yout, sm);
+            tile_forward<S, L, TV, ST>(P, itm.ty, itm.tx, xin, yout, sm);
         __syncthreads();
     }
 }
@@ -1504,12 +1504,12 @@ hipError_t MISR_FN(launch_upcurv_s)(int key, int code, int grid, hipStream_t s, 
         LAUNCH(l, StBF16);
 
 hipError_t MISR_FN(launch_forward_s)(int key, int stype, int grid, hipStream_t s, const Proj *projs,
-                                     const Item *items, int n, void *y) {
+                                     const Item *items, int n, const void *x, void *y) {
     if ((key >> 8) > 2) return hipErrorInvalidValue;
     const int Lp = key & 255;
 #define LAUNCH(l, ST)                                                                            \
     hipLaunchKernelGGL((k_forward<MISR_SCALE, l, tv, ST>), dim3(grid), dim3(kNTI), 0, s, projs, \
-                       items, n, y)
+                       items, n, x, y)
 #define X(l)                                         \
     if (Lp == l) {                                   \
         MISR_VARIANT(key, MISR_STYPES(LAUNCH, l))    \

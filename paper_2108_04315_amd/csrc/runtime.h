@@ -32,7 +32,7 @@ hipError_t launch_image(int S, int Lp, int grid, hipStream_t stream, const Proj 
                         const Item *items, const int *n_items, double *partials, int kind,
                         int code);
 hipError_t launch_forward(int S, int Lp, int grid, hipStream_t stream, const Proj *projs,
-                          const Item *items, int n, int stype, void *y);
+                          const Item *items, int n, int stype, const void *x, void *y);
 hipError_t launch_adjoint(int S, int Lp, int grid, hipStream_t stream, const Proj *projs,
                           const Item *items, int n, int stype, const void *r, float *x);
 // general operators (general_kernels.hip): one pass over a class of general
@@ -55,6 +55,19 @@ hipError_t launch_cost_out(hipStream_t stream, const double *partials, int nitem
                            double *out);
 hipError_t launch_fill(hipStream_t stream, float *p, long long n, float v);
 hipError_t launch_finalize(hipStream_t stream, const Proj *projs, int nproj, int stype);
+// Writes up to kPutSegs short arrays, passed by value with the launch, to
+// device memory (no host-to-device copy); at most kPutBytes in all, each a
+// multiple of 4 bytes.
+constexpr int kPutSegs = 7, kPutBytes = 3456;
+struct PutArgs {
+    unsigned *dst[kPutSegs];
+    int words[kPutSegs];
+    int n;
+    unsigned w[kPutBytes / 4];
+};
+hipError_t launch_put(hipStream_t stream, const PutArgs &a);
+// Copies a solve's final state (ScgState).
+hipError_t launch_copy_state(hipStream_t stream, ScgState *dst, const ScgState *src);
 // start point into x (caller storage st): kind 1 bicubic of frame 0, 2 multi-image
 // interpolation
 hipError_t launch_init(hipStream_t stream, int kind, const InitArgs &a, const void *y, void *x,
@@ -220,6 +233,7 @@ struct SolveBufs {
         if ((e = g0.ensure(n * 4)) != hipSuccess) return e;
         return g1.ensure(n * 4);
     }
+    size_t bytes() const { return x1.n + p0.n + p1.n + g0.n + g1.n + x0w.n + res.n; }
     // an untiled solve with parameters p over n HR pixels
     hipError_t ensure_view(long long n, const misr_params &p) {
         hipError_t e = ensure(n, view_esize(p));
@@ -241,9 +255,17 @@ struct TileSet {
 struct PlanDev {
     DevMem projs, items, items_u, counts, states, partials, partials_u, traces, refs, halos;
     int n_iter_max = 0;
-    size_t trace_ns = 0;
     hipGraphExec_t exec = nullptr;
     std::string graph_key;
+    // What each array on the device holds (its bytes as last uploaded, and the
+    // allocation they went to), so that a call uploads only what differs; the
+    // states are rewritten by the kernels of a solve (states_dirty).
+    struct Held {
+        void *p = nullptr;
+        std::vector<unsigned char> b;
+    };
+    Held held[7];
+    bool states_dirty = true;
     ~PlanDev() {
         if (exec) (void)hipGraphExecDestroy(exec);
     }

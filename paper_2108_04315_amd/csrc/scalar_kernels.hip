@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
+#include "runtime.h"
 
 namespace misr {
 
@@ -221,6 +222,23 @@ __global__ void __launch_bounds__(kNT) k_cost_out(const double *__restrict__ par
 }
 
 // ----------------------------------------------------------- small kernels
+// Short plan arrays (views, states) travel with the launch: one kernel in
+// stream order instead of a staged copy from pageable memory per array.
+__global__ void __launch_bounds__(64) k_put(PutArgs a) {
+    int at = 0;
+    for (int i = 0; i < a.n; ++i) {
+        for (int q = threadIdx.x; q < a.words[i]; q += 64) a.dst[i][q] = a.w[at + q];
+        at += a.words[i];
+    }
+}
+
+__global__ void __launch_bounds__(64) k_copy_state(ScgState *dst, const ScgState *src) {
+    if (threadIdx.x < kStW)
+        reinterpret_cast<unsigned long long *>(dst)[threadIdx.x] =
+            reinterpret_cast<const unsigned long long *>(src)[threadIdx.x];
+}
+static_assert(kStW <= 64, "one wave copies a state");
+
 __global__ void k_fill_f32(float *p, long long n, float v) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x)
@@ -432,7 +450,8 @@ __global__ void k_upsample(InitArgs a, const void *y, void *x, int st) {
                                   const Proj *projs, const Item *items, const int *n_items,    \
                                   double *partials);                                           \
     hipError_t launch_forward_s##s(int Lp, int stype, int grid, hipStream_t st,                \
-                                   const Proj *projs, const Item *items, int n, void *y);      \
+                                   const Proj *projs, const Item *items, int n, const void *x,  \
+                                   void *y);                                                   \
     hipError_t launch_adjoint_s##s(int Lp, int stype, int grid, hipStream_t st,                \
                                    const Proj *projs, const Item *items, int n, const void *r, \
                                    float *x);
@@ -496,9 +515,9 @@ hipError_t launch_image(int S, int Lp, int grid, hipStream_t stream, const Proj 
 }
 
 hipError_t launch_forward(int S, int Lp, int grid, hipStream_t stream, const Proj *projs,
-                          const Item *items, int n, int stype, void *y) {
+                          const Item *items, int n, int stype, const void *x, void *y) {
 #define X(s) \
-    if (S == s) return launch_forward_s##s(Lp, stype, grid, stream, projs, items, n, y);
+    if (S == s) return launch_forward_s##s(Lp, stype, grid, stream, projs, items, n, x, y);
     MISR_SCALES(X)
 #undef X
     return hipErrorInvalidValue;
@@ -564,6 +583,16 @@ hipError_t launch_init(hipStream_t stream, int kind, const InitArgs &a, const vo
     else
         hipLaunchKernelGGL(k_interpolate, dim3((unsigned)blocks), dim3(256), 0, stream, a, y, x,
                            st);
+    return hipGetLastError();
+}
+
+hipError_t launch_put(hipStream_t stream, const PutArgs &a) {
+    hipLaunchKernelGGL(k_put, dim3(1), dim3(64), 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_state(hipStream_t stream, ScgState *dst, const ScgState *src) {
+    hipLaunchKernelGGL(k_copy_state, dim3(1), dim3(64), 0, stream, dst, src);
     return hipGetLastError();
 }
 
