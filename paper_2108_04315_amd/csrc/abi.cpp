@@ -505,9 +505,23 @@ static misr_status build_general(misr_op *op, const misr_geometry *g) {
         hd.K = K;
         std::vector<float> ker;
         if (general_mf_plan(g, &hd, &ker)) {
-            MISR_HIP(op->gker.ensure(ker.size() * 4));
-            MISR_HIP(hipMemcpy(op->gker.p, ker.data(), ker.size() * 4, hipMemcpyHostToDevice));
+            // the kernels, then their taps by position phase (zero past Q):
+            // taps (t, t2) of phase (a, b) are C[a + s t][b + s t2]
+            const int Q = hd.Q, NT = (Q + s - 1) / s, QP = s * NT;
+            std::vector<float> both(ker);
+            both.resize((size_t)K * (Q * Q + QP * QP), 0.f);
+            float *pk = both.data() + (size_t)K * Q * Q;
+            for (int k = 0; k < K; ++k)
+                for (int al = 0; al < Q; ++al)
+                    for (int be = 0; be < Q; ++be) {
+                        const int ph = (al % s) * s + be % s, tp = (al / s) * NT + be / s;
+                        pk[((size_t)k * s * s + ph) * NT * NT + tp] =
+                            ker[((size_t)k * Q + al) * Q + be];
+                    }
+            MISR_HIP(op->gker.ensure(both.size() * 4));
+            MISR_HIP(hipMemcpy(op->gker.p, both.data(), both.size() * 4, hipMemcpyHostToDevice));
             hd.gker = op->gker.as<float>();
+            hd.gkp = hd.gker + (size_t)K * Q * Q;
             MISR_HIP(op->opdev.ensure(sizeof(OpDev)));
             MISR_HIP(hipMemcpy(op->opdev.p, &hd, sizeof hd, hipMemcpyHostToDevice));
             return MISR_OK;
@@ -518,6 +532,7 @@ static misr_status build_general(misr_op *op, const misr_geometry *g) {
         general_warp(g, k, warp.data() + 6 * k);
         general_psf(g, k, psf.data() + (size_t)k * P * P);
     }
+    op->tv = kGenEll;   // a class of launches of its own
     // rows in parallel chunks: (columns, weights) per row, then the ELL width
     const int nt = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
     std::vector<std::vector<int>> cc(nt), len(nt);
@@ -1083,12 +1098,12 @@ struct Launcher {
         double *part = upd ? pd.partials_u.as<double>() : pd.partials.as<double>();
         const int off = upd ? (int)pl.classes.size() : 0;
         for (int c = 0; c < (int)cls.size(); ++c) {
-            // band length 0: the class of general operators
+            // band length 0: the classes of general operators
             hipError_t e =
-                cls[c].Lp == 0
+                (cls[c].Lp & 255) == 0
                     ? launch_general(cls[c].count, s, pd.projs.as<Proj>(), items + cls[c].start,
                                      cnt() + off + c, part + (size_t)cls[c].start * kNV, kind,
-                                     cls[c].S)
+                                     cls[c].S, cls[c].Lp >> 8 == kGenEll)
                     : launch_image(cls[c].S, cls[c].Lp, cls[c].count, s, pd.projs.as<Proj>(),
                                    items + cls[c].start, cnt() + off + c,
                                    part + (size_t)cls[c].start * kNV, kind, pl.code());
@@ -1232,7 +1247,7 @@ extern "C" misr_status misr_forward(const misr_op *cop, misr_dtype dt, const voi
         MISR_HIP(launch_general_forward(
             (hipStream_t)stream, op->opdev.as<OpDev>(),
             (long long)op->K * (op->H / op->s) * (op->W / op->s), (const float *)x, (float *)y,
-            op->host.mf ? mf_lr_tiles(op->H, op->W, op->s, op->K) : 0));
+            op->host.mf ? mf_lr_tiles(op->H, op->W, op->s, op->K) : 0, op->s));
         return MISR_OK;
     }
     Plan &pl = op->plan;
@@ -1259,7 +1274,7 @@ extern "C" misr_status misr_adjoint(const misr_op *cop, misr_dtype dt, const voi
         if (dt != MISR_F32) return set_error(MISR_E_INVAL, "general operators take FP32 images");
         MISR_HIP(launch_general_adjoint((hipStream_t)stream, op->opdev.as<OpDev>(),
                                         (long long)op->H * op->W, (const float *)r, x,
-                                        op->host.mf ? mf_hr_tiles(op->H, op->W) : 0));
+                                        op->host.mf ? mf_hr_tiles(op->H, op->W) : 0, op->s));
         return MISR_OK;
     }
     Plan &pl = op->plan;

@@ -112,17 +112,21 @@ struct StBF16 {
 };
 
 // Charbonnier penalty phi(z) = sqrt(z^2+e^2) - e and its derivative
-// psi(z) = z / sqrt(z^2+e^2); e = 0 gives |z| and sign(z), sign(0) = 0.
+// psi(z) = z / sqrt(z^2+e^2) (phi_psi_pos); e = 0 gives |z| and sign(z),
+// sign(0) = 0.
+FI void phi_psi_pos(float z, float eps, float e2, float &phi, float &psi) {
+    const float d = fmaf(z, z, e2);
+    const float r = rsq(d);
+    psi = z * r;
+    phi = z * psi / fmaf(eps, r, 1.f);
+}
 FI void phi_psi(float z, float eps, float e2, float &phi, float &psi) {
     if (eps == 0.f) {
         phi = fabsf(z);
         psi = (z > 0.f) ? 1.f : ((z < 0.f) ? -1.f : 0.f);
         return;
     }
-    const float d = fmaf(z, z, e2);
-    const float r = rsq(d);
-    psi = z * r;
-    phi = z * psi / fmaf(eps, r, 1.f);
+    phi_psi_pos(z, eps, e2, phi, psi);
 }
 
 // (psi(b + h) - psi(b)) / h, the finite-difference quotient Moller's curvature

@@ -68,18 +68,21 @@ struct OpDev {
     double gm[kMaxK][6], gi[kMaxK][6];
     double eu[kMaxK], ev[kMaxK];
     const float *gker;
+    // the same by position phase: per frame s x s phases (a, b) of NT x NT
+    // taps C[a + s t][b + s t2] (zero past Q), NT = ceil(Q / s)
+    const float *gkp;
 };
 
 // Matrix-free general kernels: the forward takes LR tiles of mf_ti(s) x
-// kMfTJ pixels (kMfCPT columns per thread), the adjoint and update HR tiles
+// kMfTJ pixels (kMfCPT rows of a column per thread), the adjoint and update HR tiles
 // of kMfTU x kMfTV pixels (four per thread).  LDS: the forward's warped
 // window holds (s (mf_ti(s) - 1) + Q) x (s (kMfTJ - 1) + Q) floats (at most
 // kMfZ); the
 // adjoint's residual and back-projection windows together at most kMfWin,
 // its copy of the kernel padded to s ceil(Q / s) rows and columns at most
 // kMfQP^2.
-constexpr int kMfCPT = 2;               // forward: LR columns per thread, 32 apart
-constexpr int kMfTJ = 32 * kMfCPT;
+constexpr int kMfCPT = 2;               // forward: LR rows per thread
+constexpr int kMfTJ = 64;
 __host__ __device__ constexpr int mf_ti(int) { return 8; }
 constexpr int kMfLRG = 1;   // LR tiles per forward work item
 constexpr int kMfTU = 16, kMfTV = 64;
@@ -96,6 +99,8 @@ constexpr int kMfWin = 7424;
 // item's tx is its role: 0 LR rows (forward, residual), 1 HR rows (adjoint,
 // prior, update).
 constexpr int kGenRows = 256;
+// Variant of a general operator's launch class: the stored (ELL) form.
+constexpr int kGenEll = 1;
 // LR vectors of a general solve: the residual term, A x and A p (two each).
 constexpr int kGenVecs = 5;
 

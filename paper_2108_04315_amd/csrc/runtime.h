@@ -38,12 +38,12 @@ hipError_t launch_adjoint(int S, int Lp, int grid, hipStream_t stream, const Pro
 // general operators (general_kernels.hip): one pass over a class of general
 // items (kind as launch_image), and the standalone FP32 operators
 hipError_t launch_general(int grid, hipStream_t stream, const Proj *projs, const Item *items,
-                          const int *n_items, double *partials, int kind, int S);
+                          const int *n_items, double *partials, int kind, int S, bool ell);
 // (mf_tiles > 0: a matrix-free operator, one workgroup per tile)
 hipError_t launch_general_forward(hipStream_t stream, const OpDev *op, long long rows,
-                                  const float *x, float *y, long long mf_tiles);
+                                  const float *x, float *y, long long mf_tiles, int S);
 hipError_t launch_general_adjoint(hipStream_t stream, const OpDev *op, long long n,
-                                  const float *r, float *x, long long mf_tiles);
+                                  const float *r, float *x, long long mf_tiles, int S);
 hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, const int *n_refs,
                          const double *partials, const double *partials_u, int phase);
 hipError_t launch_halo(hipStream_t stream, const Proj *projs, const HaloCopy *copies,

@@ -537,9 +537,10 @@ hipError_t misr_server::enqueue_image(List &L, int kind, bool fresh) {
         const int cidx = (fresh ? 2 * nc + 2 : 0) + (upd ? nc : 0) + c;
         // band length 0: the class of general operators
         hipError_t e =
-            cls[c].Lp == 0
+            (cls[c].Lp & 255) == 0
                 ? launch_general(n, stream, L.projs.as<Proj>(), items + first, L.cnt(cidx),
-                                 part + (size_t)first * kNV, kind, cls[c].S)
+                                 part + (size_t)first * kNV, kind, cls[c].S,
+                                 cls[c].Lp >> 8 == kGenEll)
                 : launch_image(cls[c].S, cls[c].Lp, n, stream, L.projs.as<Proj>(), items + first,
                                L.cnt(cidx), part + (size_t)first * kNV, kind, code);
         if (e != hipSuccess) return e;
