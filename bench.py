@@ -37,7 +37,7 @@ WORKLOAD = ("plain2048: 4 LR frames 1024x1024 f32 -> 2048x2048 HR (x2), {0,1/2}^
             "lambda 0.01 alpha 0.4, 100 SCG passes")
 
 
-KERNEL_SOURCES = ("image_kernels.hip", "device_common.h", "internal.h")
+KERNEL_SOURCES = ("image_kernels.hip", "pass_end.h", "device_common.h", "internal.h")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_trial_plain2048_hbm_traffic.md")
 SQ_SUMMARY = os.path.join(ROOT, "profiles", "k_trial_plain2048_sq_counters.md")
 # VALU issue peak: one wave64 instruction per cycle per CU (4 SIMD16 units,

@@ -52,11 +52,17 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
     if (per > 0 && (e = traces.ensure(ns * per * sizeof(IterRec))) != hipSuccess) return e;
     n_iter_max = (int)per;
     ScgState *sd = states.as<ScgState>();
-    for (size_t j = 0; j < np; ++j) pl.projs[j].st = sd + pl.proj_solve[j];
+    for (size_t j = 0; j < np; ++j) {
+        pl.projs[j].st = sd + pl.proj_solve[j];
+        const int i = pl.proj_solve[j];
+        pl.projs[j].ref = pl.steps && !pl.apart[i] ? refs.as<SolveRef>() + i : nullptr;
+    }
     pl.refs.resize(ns);
     for (size_t i = 0; i < ns; ++i)
         pl.refs[i] = SolveRef{sd + i, per ? traces.as<IterRec>() + i * per : nullptr,
-                              pl.item0[i], pl.nitems[i], pl.item0u[i], pl.nitemsu[i]};
+                              partials.as<double>() + (size_t)pl.item0[i] * kNV,
+                              partials_u.as<double>() + (size_t)pl.item0u[i] * kNV,
+                              pl.nitems[i], pl.nitemsu[i], pl.apart[i], 0};
     // A call uploads the arrays whose bytes differ from what the device holds.
     // A repeated call on an operator differs in the views (its buffers) and,
     // after a solve, in the states: short arrays, which go with one launch
@@ -1020,6 +1026,8 @@ static void build_plan(Plan &pl, const std::vector<SolveIn> &in) {
     pl.tiled = false;
     pl.staged = false;
     pl.inits.clear();
+    pl.steps = true;
+    pl.apart.assign(in.size(), 0);
     pl.vt = in.empty() ? (int)ST_F32 : view_stype(in[0].prm);
     pl.gt = in.empty() ? (int)ST_F32 : (int)in[0].prm.img_dtype;
     pl.yt = in.empty() ? (int)ST_F32 : frame_stype(in[0].prm);
@@ -1043,6 +1051,7 @@ static void build_plan(Plan &pl, const std::vector<SolveIn> &in) {
             const SolveIn &si = in[i];
             const misr_op *op = si.op;
             init_state(pl.states[i], si.prm, (long long)op->H * op->W);
+            pl.apart[i] = op->general;
             pl.item0[i] = (int)pl.items.size();
             pl.item0u[i] = (int)pl.items_u.size();
             if (si.prm.tile_lr > 0 || iterate_fp32(si.prm)) {
@@ -1111,15 +1120,15 @@ struct Launcher {
         }
         return hipSuccess;
     }
-    hipError_t scalar(int phase) const {
-        return launch_scalar((int)pl.states.size(), s, pd.refs.as<SolveRef>(),
-                             cnt() + pl.n_states_idx(), pd.partials.as<double>(),
-                             pd.partials_u.as<double>(), phase);
+    // the SCG steps after a pass, of the solves whose passes do not end with them
+    hipError_t scalar(int kind) const {
+        if (!pl.any_apart(1)) return hipSuccess;
+        return launch_scalar((int)pl.states.size(), s, pd.refs.as<SolveRef>(), kind, 1);
     }
     hipError_t halo() const {
         if (pl.halos.empty()) return hipSuccess;
         return launch_halo(s, pd.projs.as<Proj>(), pd.halos.as<HaloCopy>(),
-                           cnt() + pl.n_states_idx() + 1, (int)pl.halos.size());
+                           cnt() + pl.n_halos_idx(), (int)pl.halos.size());
     }
 };
 
@@ -1135,13 +1144,13 @@ static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, ScgStat
     if (pl.staged) STEP(launch_scatter(s, pd.projs.as<Proj>(), np, pl.vt, pl.gt));
     STEP(Lr.image(KIND_COSTGRAD));
     STEP(Lr.halo());
-    STEP(Lr.scalar(PHASE_INIT));
+    STEP(Lr.scalar(KIND_COSTGRAD));
     STEP(Lr.image(KIND_UPCURV));
     for (int it = 0; it < n_iter; ++it) {
-        STEP(Lr.scalar(PHASE_A));
+        STEP(Lr.scalar(KIND_UPCURV));
         STEP(Lr.image(KIND_TRIAL));
         STEP(Lr.halo());
-        STEP(Lr.scalar(PHASE_B));
+        STEP(Lr.scalar(KIND_TRIAL));
         STEP(Lr.image(KIND_UPCURV));
     }
     if (last) STEP(launch_copy_state(s, last, pd.states.as<ScgState>()));
@@ -1349,6 +1358,7 @@ extern "C" misr_status misr_cost_grad(const misr_op *cop, const misr_params *prm
         pl.states[0].gglob = g;
     else
         pl.projs[0].g[1] = g;   // the init pass writes g[cur ^ 1] with cur = 0
+    pl.steps = false;
     PlanDev &pd = op->pdev;
     hipStream_t s = (hipStream_t)stream;
     MISR_HIP(pd.upload(pl, 0, s));
@@ -1515,12 +1525,24 @@ static misr_status time_pass_impl(misr_op *op, const misr_params *prm, const voi
     MISR_HIP(hipEventRecord(op->ctx->ev_in, (hipStream_t)stream));
     MISR_HIP(hipStreamWaitEvent(s, op->ctx->ev_in, 0));
     MISR_HIP(pd.upload(pl, 1, s));
-    pd.states_dirty = true;   // the scalar phases write them
+    pd.states_dirty = true;   // the SCG steps write them
     const Launcher Lr{pl, pd, s};
     MISR_HIP(Lr.image(KIND_COSTGRAD));
-    MISR_HIP(Lr.scalar(PHASE_INIT));
+    MISR_HIP(Lr.scalar(KIND_COSTGRAD));
     MISR_HIP(Lr.image(KIND_UPCURV));
-    MISR_HIP(Lr.scalar(PHASE_A));
+    MISR_HIP(Lr.scalar(KIND_UPCURV));
+    // from here on the passes leave the state as it is, an update pending
+    pl.projs[0].ref = nullptr;
+    pd.held[0].p = nullptr;   // (the view on the device is not what upload put there)
+    PutArgs put;
+    put.n = 2;
+    put.dst[0] = pd.projs.as<unsigned>();
+    put.words[0] = (int)(sizeof(Proj) / 4);
+    std::memcpy(put.w, &pl.projs[0], sizeof(Proj));
+    put.dst[1] = (unsigned *)&pd.states.as<ScgState>()->do_update;
+    put.words[1] = 1;
+    put.w[put.words[0]] = 1;
+    MISR_HIP(launch_put(s, put));
     hipEvent_t e0, e1;
     MISR_HIP(hipEventCreate(&e0));
     MISR_HIP(hipEventCreate(&e1));

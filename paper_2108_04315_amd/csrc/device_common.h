@@ -162,10 +162,53 @@ FI float psi_quot(float b, float h, float eps, float e2) {
     return fabsf(h * rB) < 1e-3f ? psi_series(b, h, rB, e2) : psi_closed(b, h, rB, e2);
 }
 
-FI double wave_sum(double v) {
+// Sums over a wave in a fixed order (a tree of halves: lane l adds lane
+// l + 32, then l + 16, 8, 4, 2, 1), N values at once, into out[0..N) (LDS).
+// Two values share a register pair after the first step and four after the
+// second (the swaps put one value's halves beside the other's), and the
+// steps within a row of 16 lanes are DPP rotations: 10 additions for 5 values
+// rather than 30, and no LDS round trip per step.
+FI double dbl_of(unsigned lo, unsigned hi) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+FI unsigned dbl_lo(double v) { return (unsigned)__double_as_longlong(v); }
+FI unsigned dbl_hi(double v) { return (unsigned)((unsigned long long)__double_as_longlong(v) >> 32); }
+// {a's lower half + its upper half, the same of b}
+FI double add_halves32(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(dbl_lo(a), dbl_lo(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(dbl_hi(a), dbl_hi(b), false, false);
+    return dbl_of(lo[0], hi[0]) + dbl_of(lo[1], hi[1]);
+}
+// the same by rows of 16: rows {a0 + a1, b0 + b1, a2 + a3, b2 + b3}
+FI double add_halves16(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(dbl_lo(a), dbl_lo(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(dbl_hi(a), dbl_hi(b), false, false);
+    return dbl_of(lo[0], hi[0]) + dbl_of(lo[1], hi[1]);
+}
+template <int R>
+FI double add_ror(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)dbl_lo(v), 0x120 + R, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)dbl_hi(v), 0x120 + R, 0xf, 0xf, true);
+    return v + dbl_of((unsigned)lo, (unsigned)hi);
+}
+template <int N>
+FI void wave_sums(double (&v)[N], double *out) {
+    constexpr int N2 = (N + 1) / 2, N4 = (N2 + 1) / 2;
+    const int lane = threadIdx.x & 63, row = lane >> 4;
+    double h[N2], r[N4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;
+    for (int i = 0; i < N2; ++i) h[i] = add_halves32(v[2 * i], v[min(2 * i + 1, N - 1)]);
+#pragma unroll
+    for (int i = 0; i < N4; ++i) {
+        r[i] = add_halves16(h[2 * i], h[min(2 * i + 1, N2 - 1)]);
+        r[i] = add_ror<8>(r[i]);
+        r[i] = add_ror<4>(r[i]);
+        r[i] = add_ror<2>(r[i]);
+        r[i] = add_ror<1>(r[i]);
+        // rows hold values 4 i + 0, 2, 1, 3
+        const int q = 4 * i + ((row & 1) << 1 | row >> 1);
+        if ((lane & 15) == 0 && q < N) out[q] = r[i];
+    }
 }
 
 // Sums N per-thread values over an NT-thread workgroup in a fixed order and
@@ -173,12 +216,7 @@ FI double wave_sum(double v) {
 // N * NT/64 doubles.
 template <int N, int NT>
 FI void block_sum_store(double (&v)[N], double *out, double *red) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
-    if (lane == 0)
-#pragma unroll
-        for (int i = 0; i < N; ++i) red[wid * N + i] = v[i];
+    wave_sums<N>(v, red + (threadIdx.x >> 6) * N);
     __syncthreads();
     if (threadIdx.x < N) {
         double s = 0.0;

@@ -31,6 +31,7 @@
 #include <utility>
 
 #include "device_common.h"
+#include "pass_end.h"
 
 #ifndef MISR_SCALE
 #error "compile with -DMISR_SCALE=<s>"
@@ -942,7 +943,7 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
         }
     }
     double v[5] = {e_data, e_reg, gg, ggk, gp};
-    block_sum_store<5, kNTI>(v, part, red);
+    pass_end<5, kNTI>(v, part, red, P, mode);
 }
 
 // Data part of the curvature over the owned LR pixels (all edges are
@@ -1132,7 +1133,7 @@ FI void tile_upcurv(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, f
         curv_sweep<S, L, TV, true, false>(xs, ps, gam, eps, sk, o.U0, o.V0, H, W, ru0, ru1, rv0,
                                       rv1, dreg);
     double v[4] = {ap2, dreg, pp, pr};
-    block_sum_store<4, kNTI>(v, part, red);
+    pass_end<4, kNTI>(v, part, red, P, 2);
 }
 
 // y[k] = A_k x on the owned LR pixels of one tile.

@@ -122,6 +122,9 @@ struct Proj {
     int uy0, uy1, ux0, ux1;
     int ntx;             // tiles per row of the owned rectangle
     struct ScgState *st; // the solve this view belongs to
+    // banded operators: the solve's SCG steps, run by the last workgroup of
+    // each of its passes (NULL: partial sums only)
+    const struct SolveRef *ref;
     const OpDev *op;
     float *res;          // general operators: the residual term per LR row (K h w)
     // matrix-free general operators: A x[i] and A p[i] per LR row (K h w
@@ -171,7 +174,7 @@ struct Weights {
 };
 
 // Device-resident SCG state of one solve (Moller's scalars, FP64).
-struct ScgState {
+struct ScgScalars {
     double E, E0, lam, lam_bar, delta, mu, pi, rr;
     double alpha, beta, sigma, sigk;
     double E_t, Delta;
@@ -186,19 +189,25 @@ struct ScgState {
     int do_update;       // k_upcurv runs this pass
     float alpha_f, beta_f, sigk_f;
     unsigned rseed;      // per-pass seed of the stochastic rounding hash
+};
+struct ScgState : ScgScalars {
+    unsigned arrived;    // workgroups of the running pass that are done, 0 between passes
     void *xglob;         // tiled solves: the caller's whole-image x (row stride ldg)
     float *gglob;        // tiled cost_grad: the caller's whole-image gradient
     int ldg, pad2_;
     Weights wt;
 };
 
-// A solve as seen by the scalar kernel: its state, its per-pass record and
-// the range of work items (and partial sums) its views occupy.
+// A solve as seen by its SCG steps: its state, its per-pass record and the
+// partial sums of the work items its views occupy.
 struct SolveRef {
     ScgState *st;
     struct IterRec *trace;
-    int item0, nitems;     // trial-pass items (owned tiles)
-    int item0u, nitemsu;   // update-pass items (owned plus halo)
+    double *part, *part_u;   // trial-pass (owned tiles), update-pass (owned plus halo) sums
+    int nitems, nitemsu;
+    // general operators, whose steps are launches of their own: 1, in a served
+    // stream 2 until started; else 0
+    int apart, pad_;
 };
 
 // Start-point kernels (interpolation, bicubic): grid and per-frame integer

@@ -44,8 +44,8 @@ hipError_t launch_general_forward(hipStream_t stream, const OpDev *op, long long
                                   const float *x, float *y, long long mf_tiles, int S);
 hipError_t launch_general_adjoint(hipStream_t stream, const OpDev *op, long long n,
                                   const float *r, float *x, long long mf_tiles, int S);
-hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, const int *n_refs,
-                         const double *partials, const double *partials_u, int phase);
+hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, int pass,
+                         int least);
 hipError_t launch_halo(hipStream_t stream, const Proj *projs, const HaloCopy *copies,
                        const int *n_copies, int grid);
 hipError_t launch_scatter(hipStream_t stream, const Proj *projs, int nproj, int vt, int gt);
@@ -73,8 +73,8 @@ hipError_t launch_copy_state(hipStream_t stream, ScgState *dst, const ScgState *
 hipError_t launch_init(hipStream_t stream, int kind, const InitArgs &a, const void *y, void *x,
                        int st);
 
+// (also the passes of launch_scalar)
 enum { KIND_COSTGRAD = 0, KIND_TRIAL = 1, KIND_UPCURV = 2 };
-enum { PHASE_INIT = 0, PHASE_A = 1, PHASE_B = 2 };
 
 misr_status set_error(misr_status st, const char *fmt, ...);
 misr_status hip_fail(hipError_t e, const char *what);
@@ -171,11 +171,18 @@ struct Plan {
     std::vector<Item> items, items_u;
     std::vector<ScgState> states;
     std::vector<Cls> classes, classes_u;
-    std::vector<int> counts;          // trial classes, update classes, then n_states
+    std::vector<int> counts;          // trial classes, update classes, then halo copies
     std::vector<int> proj_solve;      // solve index of each view
     std::vector<int> item0, nitems;   // per solve: its range of trial items
     std::vector<int> item0u, nitemsu; // per solve: its range of update items
     std::vector<SolveRef> refs;       // device-side references (filled by upload)
+    bool steps = true;                // a solve (false: an evaluation or an operator alone)
+    std::vector<char> apart;          // per solve: SolveRef::apart
+    bool any_apart(int least) const {
+        for (char a : apart)
+            if (a >= least) return true;
+        return false;
+    }
     std::vector<HaloCopy> halos;      // halo exchanges after each trial pass
     struct Init {                     // start points computed on the device
         int kind;
@@ -195,10 +202,9 @@ struct Plan {
         counts.clear();
         for (auto &c : classes) counts.push_back(c.count);
         for (auto &c : classes_u) counts.push_back(c.count);
-        counts.push_back((int)refs.size() > 0 ? (int)refs.size() : (int)states.size());
         counts.push_back((int)halos.size());
     }
-    int n_states_idx() const { return (int)(classes.size() + classes_u.size()); }
+    int n_halos_idx() const { return (int)(classes.size() + classes_u.size()); }
 };
 
 // The iterate is FP32 in library buffers while the caller's x is 16-bit.

@@ -4,204 +4,24 @@
 #include <hip/hip_runtime.h>
 
 #include "device_common.h"
+#include "pass_end.h"
 #include "runtime.h"
 
 namespace misr {
 
-// ------------------------------------------------------------ scalar kernels
-// One workgroup per solve: sums that solve's partials in a fixed order, then
-// thread 0 runs Moller's scalar steps in FP64.
-enum Phase { PH_INIT = 0, PH_A = 1, PH_B = 2 };
-
-__device__ void scg_init(ScgState &s, const double *v) {
-    s.E = v[0] + v[1];
-    s.E0 = s.E;
-    s.rr = v[2];
-    s.pi = v[2];
-    s.mu = v[2];
-    s.alpha = 0.0;
-    s.beta = 0.0;
-    s.alpha_f = 0.f;
-    s.beta_f = 0.f;
-    s.lam_bar = 0.0;
-    s.k = 1;
-    s.it = 0;
-    s.n_success = 0;
-    s.stop = 0;
-    if (!isfinite(s.E) || !isfinite(s.rr)) {
-        s.active = 0;
-        s.stop = 2;
-        s.do_update = 0;
-        return;
-    }
-    s.active = (s.n_iter > 0);
-    s.success = 1;
-    s.cur ^= 1;          // the gradient at x0 went to g[cur ^ 1]
-    s.upd_src = s.xc;    // p[xc] is zero: the update pass sets p = -g0, x unchanged
-    s.xc ^= 1;
-    s.do_update = 1;
-    s.sigk = (s.pi > 0.0) ? s.sigma / sqrt(s.pi) : 0.0;
-    s.sigk_f = (float)s.sigk;
-}
-
-// steps 1-5 of the pass
-__device__ void scg_phase_a(ScgState &s, const double *v) {
-    if (!s.active) return;
-    if (s.success) {
-        s.delta = v[0] + v[1];
-        s.pi = v[2];
-        s.mu = v[3];
-    }
-    if (s.rr == 0.0) {
-        s.active = 0;
-        s.stop = 1;
-        return;
-    }
-    if (!isfinite(s.delta)) {
-        s.active = 0;
-        s.stop = 2;
-        return;
-    }
-    double d = s.delta + (s.lam - s.lam_bar) * s.pi;
-    if (d <= 0.0) {
-        s.lam_bar = 2.0 * (s.lam - d / s.pi);
-        d = -d + s.lam * s.pi;
-        s.lam = s.lam_bar;
-    }
-    s.delta = d;
-    s.alpha = s.mu / d;
-    if (!isfinite(s.alpha)) {
-        s.active = 0;
-        s.stop = 2;
-        return;
-    }
-    s.alpha_f = (float)s.alpha;
-    s.rseed = mix32(0x51ed270bu + (unsigned)s.it);
-}
-
-// steps 6-9 of the pass
-__device__ void scg_phase_b(ScgState &s, const double *v, IterRec *trace) {
-    s.do_update = 0;
-    if (!s.active) return;
-    const double rr0 = s.rr;   // |r|^2 at the pass's start (mu = p . r used this r)
-    const double Et = v[0] + v[1];
-    s.E_t = Et;
-    if (!isfinite(Et)) {
-        s.active = 0;
-        s.stop = 2;
-        s.Delta = 0.0;
-    } else {
-        const double Delta = 2.0 * s.delta * (s.E - Et) / (s.mu * s.mu);
-        s.Delta = Delta;
-        if (Delta >= 0.0) {
-            const double gg = v[2], ggk = v[3], gp = v[4];
-            s.E = Et;
-            s.lam_bar = 0.0;
-            s.success = 1;
-            s.n_success++;
-            s.beta = (s.k % s.N == 0) ? 0.0 : (gg - ggk) / s.mu;
-            s.rr = gg;
-            s.cur ^= 1;
-            s.upd_src = s.xc;
-            s.xc ^= 1;
-            s.do_update = 1;
-            s.beta_f = (float)s.beta;
-            const double pn = gg - 2.0 * s.beta * gp + s.beta * s.beta * s.pi;
-            s.sigk = (pn > 0.0) ? s.sigma / sqrt(pn) : 0.0;
-            s.sigk_f = (float)s.sigk;
-            if (Delta >= 0.75) s.lam *= 0.25;
-        } else {
-            s.lam_bar = s.lam;
-            s.success = 0;
-        }
-        if (Delta < 0.25) s.lam += s.delta * (1.0 - Delta) / s.pi;
-    }
-    if (trace) {
-        IterRec &r = trace[s.it];
-        r.E = s.E;
-        r.E_t = s.E_t;
-        r.delta = s.delta;
-        r.mu = s.mu;
-        r.alpha = s.alpha;
-        r.Delta = s.Delta;
-        r.lam = s.lam;
-        r.pi = s.pi;
-        r.rr = rr0;
-        r.success = (s.do_update != 0);
-        r.pad_ = 0;
-    }
-    s.k++;
-    s.it++;
-    if (s.it >= s.n_iter) s.active = 0;
-}
-
-// partials: per-item sums of the trial pass (init, phase B); partials_u: of
-// the update pass (phase A).
-// The solve's state is copied into LDS by 8-byte words while its partial
-// sums are loaded (both only need the SolveRef), updated there by thread 0
-// and copied back, so the kernel waits on global memory twice per solve
-// rather than once per dependent access.
-constexpr int kStW = (int)(sizeof(ScgState) / 8);
-static_assert(sizeof(ScgState) % 8 == 0 && kStW <= kNT, "state copied by 8-byte words");
-// Threads of the scalar kernel (a solve's partial sums, one row per work
-// item, four loads each in flight per round; 1024 threads measured slower).
-constexpr int kST = kNT;
-
-__global__ void __launch_bounds__(kST) k_scalar(const SolveRef *refs, const int *n_refs,
-                                                const double *__restrict__ partials,
-                                                const double *__restrict__ partials_u,
-                                                int phase) {
-    __shared__ double red[kNV * (kST / 64)];
-    __shared__ double tot[kNV];
-    __shared__ ScgState sst;
-    unsigned long long *sw = reinterpret_cast<unsigned long long *>(&sst);
-    const int ns = *n_refs;
-    // the launch grid never exceeds the SolveRef array, so the first ref is
-    // read without waiting for the count
-    SolveRef ref = refs[blockIdx.x];
-    for (int sv = blockIdx.x; sv < ns; sv += gridDim.x) {
-        if (sv != (int)blockIdx.x) ref = refs[sv];
-        unsigned long long *gw = reinterpret_cast<unsigned long long *>(ref.st);
-        if (threadIdx.x < kStW) sw[threadIdx.x] = gw[threadIdx.x];
-        const double *pt = (phase == PH_A) ? partials_u : partials;
-        const int i0 = (phase == PH_A) ? ref.item0u : ref.item0;
-        const int ni = (phase == PH_A) ? ref.nitemsu : ref.nitems;
-        // four items per step, all their loads issued before the additions
-        // (a solve may hold thousands of items); past the end an item is
-        // loaded from a valid address and counted as zero, so each thread
-        // adds its items in the same order whatever the count, and in one
-        // memory round trip per kSU x kST items
-        constexpr int kSU = 4;   // (eight measured slower)
-        double v[kNV] = {0, 0, 0, 0, 0, 0};
-        const int end = i0 + ni;
-        for (int i = i0 + threadIdx.x; i < end; i += kSU * kST) {
-            double t[kSU][kNV];
-#pragma unroll
-            for (int a = 0; a < kSU; ++a) {
-                const int j = (i + a * kST < end) ? i + a * kST : i;
-#pragma unroll
-                for (int q = 0; q < kNV; ++q) t[a][q] = pt[(long long)j * kNV + q];
-            }
-#pragma unroll
-            for (int a = 0; a < kSU; ++a)
-#pragma unroll
-                for (int q = 0; q < kNV; ++q) v[q] += (i + a * kST < end) ? t[a][q] : 0.0;
-        }
-        // the sums are used only where the phase needs them (scg_phase_a
-        // reads them after an accepted pass only)
-        block_sum_store<kNV, kST>(v, tot, red);   // its barriers also publish sst
-        if (threadIdx.x == 0) {
-            if (phase == PH_INIT)
-                scg_init(sst, tot);
-            else if (phase == PH_A)
-                scg_phase_a(sst, tot);
-            else
-                scg_phase_b(sst, tot, ref.trace);
-        }
-        __syncthreads();
-        if (threadIdx.x < kStW) gw[threadIdx.x] = sw[threadIdx.x];
-        __syncthreads();
-    }
+// ------------------------------------------------------------ scalar kernel
+// The SCG steps after a pass of the general operators' solves, one workgroup
+// per solve (banded operators run them at the end of the pass, pass_end.h);
+// solves with apart >= least.
+__global__ void __launch_bounds__(kEndRows) k_scalar(const SolveRef *refs, int pass,
+                                                     int least) {
+    __shared__ double red[kNV * (kEndRows / 64)];
+    const AS4 SolveRef *rp = cst(refs) + blockIdx.x;
+    if (rp->apart < least) return;
+    sum_rows<5>(glb((const double *)(pass == 2 ? rp->part_u : rp->part)),
+                pass == 2 ? rp->nitemsu : rp->nitems, red, [](const AS1 double *a) { return *a; });
+    __syncthreads();
+    if (threadIdx.x == 0) scg_steps<5>(rp, red, pass, false);
 }
 
 // Sums one solve's partials into out[0..3) = {J, E_data, E_reg} (cost only).
@@ -233,11 +53,11 @@ __global__ void __launch_bounds__(64) k_put(PutArgs a) {
 }
 
 __global__ void __launch_bounds__(64) k_copy_state(ScgState *dst, const ScgState *src) {
-    if (threadIdx.x < kStW)
+    static_assert(sizeof(ScgState) % 8 == 0 && sizeof(ScgState) <= 512, "one wave copies a state");
+    if (threadIdx.x < sizeof(ScgState) / 8)
         reinterpret_cast<unsigned long long *>(dst)[threadIdx.x] =
             reinterpret_cast<const unsigned long long *>(src)[threadIdx.x];
 }
-static_assert(kStW <= 64, "one wave copies a state");
 
 __global__ void k_fill_f32(float *p, long long n, float v) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
@@ -286,7 +106,7 @@ __global__ void __launch_bounds__(256) k_halo(const Proj *__restrict__ projs,
         const HaloCopy hc = copies[c];
         const Proj &A = projs[hc.src];
         const Proj &B = projs[hc.dst];
-        const int g = A.st->cur ^ 1;
+        const int g = A.st->cur;
         const long long lda = A.ld, ldb = B.ld;
         const float *__restrict__ src =
             A.g[g] + (long long)(hc.gy - A.gy0) * lda + hc.gx - A.gx0;
@@ -532,10 +352,9 @@ hipError_t launch_adjoint(int S, int Lp, int grid, hipStream_t stream, const Pro
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, const int *n_refs,
-                         const double *partials, const double *partials_u, int phase) {
-    hipLaunchKernelGGL(k_scalar, dim3(grid), dim3(kST), 0, stream, refs, n_refs, partials,
-                       partials_u, phase);
+hipError_t launch_scalar(int grid, hipStream_t stream, const SolveRef *refs, int pass,
+                         int least) {
+    hipLaunchKernelGGL(k_scalar, dim3(grid), dim3(kEndRows), 0, stream, refs, pass, least);
     return hipGetLastError();
 }
 

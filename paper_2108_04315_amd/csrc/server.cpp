@@ -135,12 +135,11 @@ struct misr_server {
     // come first and the newly admitted ones' after, so that the init passes
     // of the new solves run over a sub-range of each class.
     // Device counts: [0,nc) trial items per class, [nc,2nc) update items per
-    // class, 2nc solves, 2nc+1 halo copies, then the same four for the new
-    // solves only at offset 2nc+2.
+    // class, 2nc halo copies, then the same three for the new solves only at
+    // offset 2nc+1.
     struct List {
         Plan pl;
         std::vector<int> nb, nbu;            // per class: first trial / update item of the new solves
-        std::vector<SolveRef> refs_new;      // the new solves only
         std::vector<HaloCopy> halos_new;     // halo copies of the new solves only
         std::vector<int> counts;
         // device copies of the arrays above, all in one block (one upload)
@@ -148,7 +147,7 @@ struct misr_server {
             void *p = nullptr;
             template <typename T>
             T *as() const { return (T *)p; }
-        } projs, items, items_u, counts_d, refs, drefs_new, halos, halos_new_d;
+        } projs, items, items_u, counts_d, refs, halos, halos_new_d;
         DevMem blob, partials, partials_u;
         Pinned stage;                        // the packed arrays, pinned for the upload
         int nc() const { return (int)pl.classes.size(); }
@@ -186,7 +185,7 @@ struct misr_server {
     int max_idle() const { return cfg.max_idle_ops > 0 ? cfg.max_idle_ops : 8; }
     hipError_t enqueue_init(List &L, const std::vector<SReq *> &rs);
     hipError_t enqueue_image(List &L, int kind, bool fresh);
-    hipError_t enqueue_scalar(List &L, int phase, bool fresh);
+    hipError_t enqueue_scalar(List &L, int kind, bool fresh);
     hipError_t enqueue_halo(List &L, bool fresh);
     // storage code of the image launches (every admitted request shares
     // img_dtype and x_work)
@@ -262,7 +261,7 @@ static size_t list_bytes(const misr_request &q, bool general) {
     }
     const size_t per = (size_t)(ni + nu) * (sizeof(Item) + kNV * sizeof(double)) +
                        (size_t)nviews * sizeof(Proj) + (size_t)nhalo * 2 * sizeof(HaloCopy) +
-                       2 * sizeof(SolveRef);
+                       sizeof(SolveRef);
     return 2 * per;
 }
 
@@ -427,10 +426,13 @@ hipError_t misr_server::build_list(List &L, const std::vector<SReq *> &rs) {
     pl.classes.clear();
     pl.classes_u.clear();
     pl.refs.clear();
+    pl.proj_solve.clear();
+    pl.apart.clear();
+    pl.item0.clear();
+    pl.item0u.clear();
     pl.halos.clear();
     L.nb.clear();
     L.nbu.clear();
-    L.refs_new.clear();
     L.halos_new.clear();
     std::map<std::pair<int, int>, std::vector<SReq *>> groups;
     std::vector<std::pair<int, int>> order;
@@ -457,12 +459,16 @@ hipError_t misr_server::build_list(List &L, const std::vector<SReq *> &rs) {
                       pl.items, pl.items_u, pl.halos);
             r->nviews = (int)pl.projs.size() - r->view0;
             for (int j = r->view0; j < (int)pl.projs.size(); ++j) pl.projs[j].st = r->st_dev;
-            pl.refs.push_back(SolveRef{r->st_dev, r->trace_dev, i0, (int)pl.items.size() - i0,
-                                       iu0, (int)pl.items_u.size() - iu0});
-            if (r->fresh) {
-                L.refs_new.push_back(pl.refs.back());
+            pl.proj_solve.resize(pl.projs.size(), (int)pl.refs.size());
+            pl.apart.push_back(r->op->general ? (r->fresh ? 2 : 1) : 0);
+            // (its partial sums' rows: below, once they are allocated)
+            pl.refs.push_back(SolveRef{r->st_dev, r->trace_dev, nullptr, nullptr,
+                                       (int)pl.items.size() - i0, (int)pl.items_u.size() - iu0,
+                                       pl.apart.back(), 0});
+            pl.item0.push_back(i0);
+            pl.item0u.push_back(iu0);
+            if (r->fresh)
                 L.halos_new.insert(L.halos_new.end(), pl.halos.begin() + h0, pl.halos.end());
-            }
         }
         c.count = (int)pl.items.size() - c.start;
         cu.count = (int)pl.items_u.size() - cu.start;
@@ -475,13 +481,11 @@ hipError_t misr_server::build_list(List &L, const std::vector<SReq *> &rs) {
     L.counts.clear();
     for (auto &c : pl.classes) L.counts.push_back(c.count);
     for (auto &c : pl.classes_u) L.counts.push_back(c.count);
-    L.counts.push_back((int)pl.refs.size());
     L.counts.push_back((int)pl.halos.size());
     for (int c = 0; c < nc; ++c)
         L.counts.push_back(pl.classes[c].start + pl.classes[c].count - L.nb[c]);
     for (int c = 0; c < nc; ++c)
         L.counts.push_back(pl.classes_u[c].start + pl.classes_u[c].count - L.nbu[c]);
-    L.counts.push_back((int)L.refs_new.size());
     L.counts.push_back((int)L.halos_new.size());
     const size_t np = pl.projs.size(), ni = pl.items.size(), nu = pl.items_u.size(),
                  ns = pl.refs.size(), nh = pl.halos.size(), nhn = L.halos_new.size();
@@ -494,7 +498,6 @@ hipError_t misr_server::build_list(List &L, const std::vector<SReq *> &rs) {
                {&L.items_u, pl.items_u.data(), nu * sizeof(Item)},
                {&L.counts_d, L.counts.data(), L.counts.size() * sizeof(int)},
                {&L.refs, pl.refs.data(), ns * sizeof(SolveRef)},
-               {&L.drefs_new, L.refs_new.data(), L.refs_new.size() * sizeof(SolveRef)},
                {&L.halos, pl.halos.data(), nh * sizeof(HaloCopy)},
                {&L.halos_new_d, L.halos_new.data(), nhn * sizeof(HaloCopy)}};
     size_t total = 0;
@@ -509,13 +512,23 @@ hipError_t misr_server::build_list(List &L, const std::vector<SReq *> &rs) {
         (void)hipGetLastError();
         return e;
     }
-    char *hp = (char *)L.stage.h, *dp = L.blob.as<char>();
+    char *dp = L.blob.as<char>();
+    for (auto &u : ups) {
+        u.d->p = dp;
+        dp += (u.n + 255) & ~(size_t)255;
+    }
+    for (size_t j = 0; j < np; ++j) {
+        const int i = pl.proj_solve[j];
+        pl.projs[j].ref = pl.apart[i] ? nullptr : L.refs.as<SolveRef>() + i;
+    }
+    for (size_t i = 0; i < ns; ++i) {
+        pl.refs[i].part = L.partials.as<double>() + (size_t)pl.item0[i] * kNV;
+        pl.refs[i].part_u = L.partials_u.as<double>() + (size_t)pl.item0u[i] * kNV;
+    }
+    char *hp = (char *)L.stage.h;
     for (auto &u : ups) {
         if (u.n) std::memcpy(hp, u.h, u.n);
-        u.d->p = dp;
-        const size_t step = (u.n + 255) & ~(size_t)255;
-        hp += step;
-        dp += step;
+        hp += (u.n + 255) & ~(size_t)255;
     }
     return hipMemcpyAsync(L.blob.p, L.stage.h, (size_t)(hp - (char *)L.stage.h),
                           hipMemcpyHostToDevice, stream);
@@ -534,7 +547,7 @@ hipError_t misr_server::enqueue_image(List &L, int kind, bool fresh) {
         const int first = fresh ? (upd ? L.nbu[c] : L.nb[c]) : cls[c].start;
         const int n = cls[c].start + cls[c].count - first;
         if (n <= 0) continue;
-        const int cidx = (fresh ? 2 * nc + 2 : 0) + (upd ? nc : 0) + c;
+        const int cidx = (fresh ? 2 * nc + 1 : 0) + (upd ? nc : 0) + c;
         // band length 0: the class of general operators
         hipError_t e =
             (cls[c].Lp & 255) == 0
@@ -548,13 +561,11 @@ hipError_t misr_server::enqueue_image(List &L, int kind, bool fresh) {
     return hipSuccess;
 }
 
-hipError_t misr_server::enqueue_scalar(List &L, int phase, bool fresh) {
-    const int nc = L.nc();
-    const int n = fresh ? (int)L.refs_new.size() : (int)L.pl.refs.size();
-    if (n == 0) return hipSuccess;
-    return launch_scalar(n, stream, fresh ? L.drefs_new.as<SolveRef>() : L.refs.as<SolveRef>(),
-                         L.cnt((fresh ? 2 * nc + 2 : 0) + 2 * nc), L.partials.as<double>(),
-                         L.partials_u.as<double>(), phase);
+// The SCG steps after a pass, of the solves whose passes do not end with them.
+hipError_t misr_server::enqueue_scalar(List &L, int kind, bool fresh) {
+    const int least = fresh ? 2 : 1;
+    if (!L.pl.any_apart(least)) return hipSuccess;
+    return launch_scalar((int)L.pl.refs.size(), stream, L.refs.as<SolveRef>(), kind, least);
 }
 
 hipError_t misr_server::enqueue_halo(List &L, bool fresh) {
@@ -563,7 +574,7 @@ hipError_t misr_server::enqueue_halo(List &L, bool fresh) {
     if (n == 0) return hipSuccess;
     return launch_halo(stream, L.projs.as<Proj>(),
                        fresh ? L.halos_new_d.as<HaloCopy>() : L.halos.as<HaloCopy>(),
-                       L.cnt((fresh ? 2 * nc + 2 : 0) + 2 * nc + 1), (int)n);
+                       L.cnt((fresh ? 2 * nc + 1 : 0) + 2 * nc), (int)n);
 }
 
 // Init of the newly admitted solves over their sub-range of the list: start
@@ -583,9 +594,9 @@ hipError_t misr_server::enqueue_init(List &L, const std::vector<SReq *> &rs) {
                                view_stype(r->req.params), (int)r->req.params.img_dtype);
     if (e == hipSuccess) e = enqueue_image(L, KIND_COSTGRAD, true);
     if (e == hipSuccess) e = enqueue_halo(L, true);
-    if (e == hipSuccess) e = enqueue_scalar(L, PHASE_INIT, true);
+    if (e == hipSuccess) e = enqueue_scalar(L, KIND_COSTGRAD, true);
     if (e == hipSuccess) e = enqueue_image(L, KIND_UPCURV, true);
-    if (e == hipSuccess) e = enqueue_scalar(L, PHASE_A, true);
+    if (e == hipSuccess) e = enqueue_scalar(L, KIND_UPCURV, true);
     return e;
 }
 
@@ -753,17 +764,17 @@ void misr_server::run() {
             for (SReq *r : run) any_fresh |= r->fresh;
             if (e == hipSuccess && any_fresh) e = enqueue_init(C.list, run);
             for (SReq *r : run) r->fresh = false;
-            // Each pass ends with steps 1-5 of the next one (phase A), so that
+            // Each pass ends with steps 1-5 of the next one (pass_end.h), so that
             // no partial sums outlive a cycle: the next cycle's list may place
             // a running solve's items elsewhere.  After a solve's last pass
-            // phase A finds it inactive and changes nothing.
+            // those steps find it inactive and change nothing.
             List &L = C.list;
             for (int ep = 0; ep < n_ep && e == hipSuccess; ++ep) {
                 e = enqueue_image(L, KIND_TRIAL, false);
                 if (e == hipSuccess) e = enqueue_halo(L, false);
-                if (e == hipSuccess) e = enqueue_scalar(L, PHASE_B, false);
+                if (e == hipSuccess) e = enqueue_scalar(L, KIND_TRIAL, false);
                 if (e == hipSuccess) e = enqueue_image(L, KIND_UPCURV, false);
-                if (e == hipSuccess) e = enqueue_scalar(L, PHASE_A, false);
+                if (e == hipSuccess) e = enqueue_scalar(L, KIND_UPCURV, false);
             }
             // finished solves: current iterate into the caller's buffer and the
             // final state into the request's pinned slot
