@@ -41,6 +41,13 @@ FI const AS1 T *glb(const T *p) { return (const AS1 T *)p; }
 template <class T>
 FI AS1 T *glbw(T *p) { return (AS1 T *)p; }
 
+// p + i, i unsigned and below 2^30 elements: from a uniform p the access takes
+// a 32-bit lane offset instead of a 64-bit address.
+template <class T>
+FI const AS1 T *at32(const AS1 T *p, unsigned i) {
+    return (const AS1 T *)((const AS1 char *)p + i * (unsigned)sizeof(T));
+}
+
 // 32-bit mixing hash (the MurmurHash3 finaliser) of a pixel index and a seed:
 // the counter-based source of the stochastic-rounding bits.
 FI unsigned mix32(unsigned h) {

@@ -106,11 +106,6 @@ FI bool mf_lr_tile(const AS4 OpDev &op, int t, int q, int &k, int &ti, int &tj) 
     return true;
 }
 
-// p[c] by a 32-bit byte offset from a uniform base (c < 2^30).
-FI float at32(const AS1 float *p, unsigned c) {
-    return *(const AS1 float *)((const AS1 char *)p + (c << 2));
-}
-
 // e / d for 0 <= e < 2^21, d >= 1, through the float reciprocal inv = 1 / d:
 // (e + 1/2) / d lies at least 1/(2 d) from an integer, well above the
 // product's rounding error, so the truncation is exact.
@@ -253,9 +248,19 @@ FI void mf_forward(const AS4 OpDev &op, int k, int ti, int tj, V vec, float *zs,
 // the clamp only keeps the conversion defined).
 FI int mf_int(double v) { return (int)fmin(fmax(v, -1073741824.0), 1073741824.0); }
 
+constexpr int kMfRR = 4;   // rows of a residual window per wave, loaded a frame ahead
+struct MfGeo {
+    int i[4];     // the back-projection window: ua, va, ub, vb
+    float f[4];   // tile-relative origins: preimage (u, v), warped (r, c)
+};
+FI float readlane_f(float v, int k) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+
 // acc[t] += sum_k (A_k^T r_k)(pixel) for this thread's four pixels of HR
 // tile (tu, tv) (rows tu kMfTU + threadIdx.x / 64 + 4 t, column
-// tv kMfTV + threadIdx.x % 64); res(k, i, j) gives r_k.  lds: kMfWin floats
+// tv kMfTV + threadIdx.x % 64); res.value(res.load(row, j)) gives r_k (LR
+// row `row` of all frames' rows, times w).  lds: kMfWin floats
 // plus kMfQP^2, free again on return.
 //
 // Per frame: the back-projection window [ua, ub] x [va, vb] holds every
@@ -272,11 +277,19 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
     const int NT = (Q + S - 1) / S, QP = S * NT;
     const int U0 = tu * kMfTU, V0 = tv * kMfTV;
     const int U1 = min(U0 + kMfTU, H) - 1, V1 = min(V0 + kMfTV, W) - 1;
-    const int row = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int row = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool full = U0 + kMfTU <= H && V0 + kMfTV <= W;   // (uniform)
     float *cpl = lds + kMfWin;
-    for (int k = 0; k < op.K; ++k) {
+    // every frame's geometry at once, one frame per lane (in FP64 and the same
+    // for the whole tile: computed frame by frame, by all lanes alike, it was
+    // a serial chain at the head of each)
+    MfGeo gl;
+    {
+        const int k = min(lane, op.K - 1);
         const double g0 = op.gi[k][0], g1 = op.gi[k][1], g2 = op.gi[k][2];
         const double g3 = op.gi[k][3], g4 = op.gi[k][4], g5 = op.gi[k][5];
+        const double m0 = op.gm[k][0], m1 = op.gm[k][1], m2 = op.gm[k][2];
+        const double m3 = op.gm[k][3], m4 = op.gm[k][4], m5 = op.gm[k][5];
         const double eu = op.eu[k], ev = op.ev[k];
         double umin = 1e300, umax = -1e300, vmin = 1e300, vmax = -1e300;
 #pragma unroll
@@ -288,15 +301,70 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
             vmin = fmin(vmin, vc);
             vmax = fmax(vmax, vc);
         }
-        // (the same in every lane: scalar registers)
-        const int ua = uni(mf_int(floor(umin - eu)) + 1), va = uni(mf_int(floor(vmin - ev)) + 1);
-        const int ub = min(uni(mf_int(floor(umax + eu)) + 1), ua + op.ru[k] - 1);
-        const int vb = min(uni(mf_int(floor(vmax + ev)) + 1), va + op.rv[k] - 1);
-        // the tile's pixels gather from nothing on the grid: skip (uniform)
-        if (ub < 0 || ua > H - 1 || vb < 0 || va > W - 1) continue;
+        const int ua = mf_int(floor(umin - eu)) + 1, va = mf_int(floor(vmin - ev)) + 1;
+        gl.i[0] = ua;
+        gl.i[1] = va;
+        gl.i[2] = min(mf_int(floor(umax + eu)) + 1, ua + op.ru[k] - 1);
+        gl.i[3] = min(mf_int(floor(vmax + ev)) + 1, va + op.rv[k] - 1);
+        // tile-relative coordinates in FP32 (magnitudes of the tile's extent):
+        // the preimage of the tile's corner pixel (U0, V0) less the window's
+        // origin, and the warped coordinate of the window's origin less the
+        // corner pixel, both from FP64 once per tile.  A rounding that moves a
+        // pixel's first candidate by one position changes only candidates at
+        // the edge of its support, whose tent weights are zero to rounding.
+        gl.f[0] = (float)(fma(g0, (double)U0, fma(g1, (double)V0, g2)) - ua);
+        gl.f[1] = (float)(fma(g3, (double)U0, fma(g4, (double)V0, g5)) - va);
+        gl.f[2] = (float)(fma(m0, (double)ua, fma(m1, (double)va, m2)) - U0);
+        gl.f[3] = (float)(fma(m3, (double)ua, fma(m4, (double)va, m5)) - V0);
+    }
+    // frame k's window: the LR pixels (i0, j0).. of NI x NJ; whether the tile
+    // gathers from nothing on the grid (uniform)
+    struct Win {
+        int ua, va, ub, vb, i0, j0, NI, NJ;
+        bool none, rows;
+    };
+    auto window = [&](int k) {
+        Win n;
+        n.ua = __builtin_amdgcn_readlane(gl.i[0], k);
+        n.va = __builtin_amdgcn_readlane(gl.i[1], k);
+        n.ub = __builtin_amdgcn_readlane(gl.i[2], k);
+        n.vb = __builtin_amdgcn_readlane(gl.i[3], k);
+        n.none = n.ub < 0 || n.ua > H - 1 || n.vb < 0 || n.va > W - 1;
+        n.i0 = fdiv(n.ua + R, S) - NT + 1;
+        n.j0 = fdiv(n.va + R, S) - NT + 1;
+        n.NI = fdiv(n.ub + R, S) - n.i0 + 1;
+        n.NJ = fdiv(n.vb + R, S) - n.j0 + 1;
+        n.rows = n.NI <= 4 * kMfRR && n.NJ <= 64;
+        return n;
+    };
+    // A residual window of up to 16 rows and 64 columns (scales from 2, warps
+    // near the identity) is loaded by rows, one wave each, a frame ahead: its
+    // loads pass under the frame before.
+    typename Rf::Raw raw[kMfRR];
+    auto load = [&](int k, const Win &n) {
+        if (n.none || !n.rows) return;
+        const int jc = min(max(n.j0 + lane, 0), w - 1);
+#pragma unroll
+        for (int q = 0; q < kMfRR; ++q) {
+            const int i = min(max(n.i0 + min(row + 4 * q, n.NI - 1), 0), h - 1);
+            raw[q] = res.load(((i64)k * h + i) * w, jc);
+        }
+    };
+    Win nw = window(0);
+    load(0, nw);
+    for (int k = 0; k < op.K; ++k) {
+        const Win n = nw;
+        if (k + 1 < op.K) nw = window(k + 1);
+        auto ahead = [&]() {
+            if (k + 1 < op.K) load(k + 1, nw);
+        };
+        if (n.none) {
+            ahead();
+            continue;
+        }
+        const int ua = n.ua, va = n.va, ub = n.ub, vb = n.vb;
         const int RU = ub - ua + 1, RV = vb - va + 1;
-        const int i0 = fdiv(ua + R, S) - NT + 1, j0 = fdiv(va + R, S) - NT + 1;
-        const int NI = fdiv(ub + R, S) - i0 + 1, NJ = fdiv(vb + R, S) - j0 + 1;
+        const int i0 = n.i0, j0 = n.j0, NI = n.NI, NJ = n.NJ;
         float *rsm = lds, *wt = lds + NI * NJ;
         const float inj = 1.f / (float)NJ, irv = 1.f / (float)RV;
         // the back-projection window: whole cells where those fit the LDS (no
@@ -306,11 +374,23 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         const int RUC = S * (NI - NT + 1), RVC = S * (NJ - NT + 1);
         const bool whole = S > 1 && NT <= 5 && NI * NJ + RUC * RVC <= kMfWin;
         const int uw = whole ? uc : ua, vw = whole ? vc : va, RW = whole ? RVC : RV;
-        for (int e = threadIdx.x; e < NI * NJ; e += kGenRows) {
-            const int a = mf_div(e, inj), i = i0 + a, j = j0 + e - a * NJ;
-            rsm[e] = (i >= 0 && i < h && j >= 0 && j < w) ? res(k, i, j) : 0.f;
+        if (n.rows) {
+            const bool in_j = j0 + lane >= 0 && j0 + lane < w;
+#pragma unroll
+            for (int q = 0; q < kMfRR; ++q) {
+                const int a = row + 4 * q;
+                if (a < NI && lane < NJ)
+                    rsm[a * NJ + lane] =
+                        in_j && i0 + a >= 0 && i0 + a < h ? res.value(raw[q]) : 0.f;
+            }
+        } else {
+            for (int e = threadIdx.x; e < NI * NJ; e += kGenRows) {
+                const int a = mf_div(e, inj), i = i0 + a, j = j0 + e - a * NJ;
+                rsm[e] = (i >= 0 && i < h && j >= 0 && j < w)
+                             ? res.value(res.load(((i64)k * h + i) * w, j))
+                             : 0.f;
+            }
         }
-        __syncthreads();
         // The S x S positions of a cell (one LR pixel's block) take the same
         // NT x NT residuals, each position (phase) with its own taps: a
         // product of phases x taps with taps x cells, on the matrix cores in
@@ -322,47 +402,58 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
             constexpr int NTC = decltype(ntc)::value, NP = S * S, G = (NP + 3) / 4;
             const AS1 float *cp = glb(op.gkp) + (i64)k * NP * NTC * NTC;
             const int m = threadIdx.x & 3;
-            float tap[G][NTC * NTC];
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int q = 0; q < NTC * NTC; ++q)
-                    tap[g][q] = cp[min(4 * g + m, NP - 1) * NTC * NTC + q];
+            // blocks of phases taken together: as many as hold their taps in
+            // 32 registers
+            constexpr int GC = mf_cmax(1, 32 / (NTC * NTC));
             const int ncu = NI - NTC + 1, ncv = NJ - NTC + 1, nc = ncu * ncv;
             const int uo = S * (i0 + NTC - 1) - R, vo = S * (j0 + NTC - 1) - R;
             const float inv = 1.f / (float)ncv;
-            for (int e0 = 0; e0 < nc; e0 += kGenRows) {   // (uniform: every lane takes part)
-                const int e = min(e0 + (int)threadIdx.x, nc - 1);
-                const int cu = mf_div(e, inv), cv = e - cu * ncv;
-                const float *rr = rsm + (cu + NTC - 1) * NJ + cv + NTC - 1;
-                float rw[NTC * NTC];
 #pragma unroll
-                for (int t = 0; t < NTC; ++t)
+            for (int g0 = 0; g0 < G; g0 += GC) {
+                float tap[GC][NTC * NTC];
 #pragma unroll
-                    for (int t2 = 0; t2 < NTC; ++t2) rw[t * NTC + t2] = rr[-t * NJ - t2];
-                const int u0c = uo + S * cu, v0c = vo + S * cv;
-                float *wc = wt + (u0c - uw) * RW + v0c - vw;
-                // rows and columns of the cell inside the window and on the grid
-                bool inu[S], inv_[S], onu[S], onv[S];
-#pragma unroll
-                for (int a = 0; a < S; ++a) {
-                    inu[a] = whole || (u0c + a >= ua && u0c + a <= ub);
-                    inv_[a] = whole || (v0c + a >= va && v0c + a <= vb);
-                    onu[a] = u0c + a >= 0 && u0c + a < H;
-                    onv[a] = v0c + a >= 0 && v0c + a < W;
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+                for (int g = 0; g < GC; ++g)
 #pragma unroll
                     for (int q = 0; q < NTC * NTC; ++q)
-                        sum = __builtin_amdgcn_mfma_f32_4x4x1f32(tap[g][q], rw[q], sum, 0, 0, 0);
+                        tap[g][q] = cp[min(4 * (g0 + g) + m, NP - 1) * NTC * NTC + q];
+                if (g0 == 0) {
+                    ahead();
+                    __syncthreads();
+                }
+                for (int e0 = 0; e0 < nc; e0 += kGenRows) {   // (uniform: every lane takes part)
+                    const int e = min(e0 + (int)threadIdx.x, nc - 1);
+                    const int cu = mf_div(e, inv), cv = e - cu * ncv;
+                    const float *rr = rsm + (cu + NTC - 1) * NJ + cv + NTC - 1;
+                    float rw[NTC * NTC];
 #pragma unroll
-                    for (int n = 0; n < 4; ++n) {
-                        const int a = (4 * g + n) / S, b = (4 * g + n) % S;
-                        if (4 * g + n >= NP) break;
-                        const float val = onu[a] && onv[b] ? sum[n] : 0.f;
-                        if (inu[a] && inv_[b]) wc[a * RW + b] = val;
+                    for (int t = 0; t < NTC; ++t)
+#pragma unroll
+                        for (int t2 = 0; t2 < NTC; ++t2) rw[t * NTC + t2] = rr[-t * NJ - t2];
+                    const int u0c = uo + S * cu, v0c = vo + S * cv;
+                    float *wc = wt + (u0c - uw) * RW + v0c - vw;
+                    // rows and columns of the cell inside the window and on the grid
+                    bool inu[S], inv_[S], onu[S], onv[S];
+#pragma unroll
+                    for (int a = 0; a < S; ++a) {
+                        inu[a] = whole || (u0c + a >= ua && u0c + a <= ub);
+                        inv_[a] = whole || (v0c + a >= va && v0c + a <= vb);
+                        onu[a] = u0c + a >= 0 && u0c + a < H;
+                        onv[a] = v0c + a >= 0 && v0c + a < W;
+                    }
+#pragma unroll
+                    for (int g = 0; g < GC; ++g) {
+                        if (g0 + g >= G) break;
+                        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int q = 0; q < NTC * NTC; ++q)
+                            sum = __builtin_amdgcn_mfma_f32_4x4x1f32(tap[g][q], rw[q], sum, 0, 0, 0);
+#pragma unroll
+                        for (int n = 0; n < 4; ++n) {
+                            const int ph = 4 * (g0 + g) + n, a = ph / S, b = ph % S;
+                            if (ph >= NP) break;
+                            const float val = onu[a] && onv[b] ? sum[n] : 0.f;
+                            if (inu[a] && inv_[b]) wc[a * RW + b] = val;
+                        }
                     }
                 }
             }
@@ -372,6 +463,7 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         auto positions = [&]() {
             const AS1 float *cp = glb(op.gkp) + (i64)k * QP * QP;
             for (int e = threadIdx.x; e < QP * QP; e += kGenRows) cpl[e] = cp[e];
+            ahead();
             __syncthreads();
             for (int e = threadIdx.x; e < RU * RV; e += kGenRows) {
                 const int a = mf_div(e, irv);
@@ -400,37 +492,32 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         default: positions(); break;
         }
         __syncthreads();
-        const double m0 = op.gm[k][0], m1 = op.gm[k][1], m2 = op.gm[k][2];
-        const double m3 = op.gm[k][3], m4 = op.gm[k][4], m5 = op.gm[k][5];
-        const float m0f = (float)m0, m1f = (float)m1, m3f = (float)m3, m4f = (float)m4;
+        const float m0f = (float)op.gm[k][0], m1f = (float)op.gm[k][1];
+        const float m3f = (float)op.gm[k][3], m4f = (float)op.gm[k][4];
+        const float g0f = (float)op.gi[k][0], g1f = (float)op.gi[k][1];
+        const float g3f = (float)op.gi[k][3], g4f = (float)op.gi[k][4];
+        const float euf = (float)op.eu[k], evf = (float)op.ev[k];
         const int ncu = op.ncu[k], ncv = op.ncv[k];
         const bool c33 = ncu == 3 && ncv == 3;   // the near-identity warps (uniform)
-        // tile-relative coordinates in FP32 (magnitudes of the tile's extent):
-        // the preimage of the tile's corner pixel (U0, V0) less the window's
-        // origin, and the warped coordinate of the window's origin less the
-        // corner pixel, both from FP64 once per tile.  A rounding that moves a
-        // pixel's first candidate by one position changes only candidates at
-        // the edge of its support, whose tent weights are zero to rounding.
-        const float ub0 = (float)(fma(g0, (double)U0, fma(g1, (double)V0, g2)) - ua);
-        const float vb0 = (float)(fma(g3, (double)U0, fma(g4, (double)V0, g5)) - va);
-        const float rb0 = (float)(fma(m0, (double)ua, fma(m1, (double)va, m2)) - U0);
-        const float cb0 = (float)(fma(m3, (double)ua, fma(m4, (double)va, m5)) - V0);
-        const float g0f = (float)g0, g1f = (float)g1, g3f = (float)g3, g4f = (float)g4;
-        const float euf = (float)eu, evf = (float)ev;
+        const float ub0 = readlane_f(gl.f[0], k), vb0 = readlane_f(gl.f[1], k);
+        const float rb0 = readlane_f(gl.f[2], k), cb0 = readlane_f(gl.f[3], k);
+        const float rlim = (float)(RU - ncu), clim = (float)(RV - ncv), rwf = (float)RW;
+        const float *w0 = wt + (ua - uw) * RW + va - vw;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int dr = row + 4 * t, dc = lane;
-            if (U0 + dr > U1 || V0 + dc > V1) continue;
+            if (!full && (U0 + dr > U1 || V0 + dc > V1)) continue;
             // first candidate, relative to the window's origin, kept inside
-            // the window (a rounding at the edge moves it by one)
+            // the window (a rounding at the edge moves it by one); whole
+            // numbers below 2^24, exact in FP32
             const float uq = fmaf((float)dr, g0f, fmaf((float)dc, g1f, ub0)) - euf;
             const float vq = fmaf((float)dr, g3f, fmaf((float)dc, g4f, vb0)) - evf;
-            const int ous = min(max(0, (int)floorf(uq) + 1), RU - ncu);
-            const int ovs = min(max(0, (int)floorf(vq) + 1), RV - ncv);
+            const float ous = __builtin_amdgcn_fmed3f(floorf(uq) + 1.f, 0.f, rlim);
+            const float ovs = __builtin_amdgcn_fmed3f(floorf(vq) + 1.f, 0.f, clim);
             // its warped coordinate relative to the pixel
-            const float d0r = fmaf((float)ous, m0f, fmaf((float)ovs, m1f, rb0)) - (float)dr;
-            const float d0c = fmaf((float)ous, m3f, fmaf((float)ovs, m4f, cb0)) - (float)dc;
-            const float *wb = wt + (ous + ua - uw) * RW + ovs + va - vw;
+            const float d0r = fmaf(ous, m0f, fmaf(ovs, m1f, rb0)) - (float)dr;
+            const float d0c = fmaf(ous, m3f, fmaf(ovs, m4f, cb0)) - (float)dc;
+            const float *wb = w0 + (int)fmaf(ous, rwf, ovs);
             float a_t = 0.f;
             auto cand = [&](int a, int b) {
                 const float ar = a ? fmaf((float)a, m0f, d0r) : d0r;
@@ -491,8 +578,8 @@ FI float ell_row(const AS1 int *col, const AS1 float *val, int width, i64 rows, 
 // Residual term of LR row r (frame value y[r]) at forward value ax: the term
 // the adjoint consumes (2 r, or psi(r) for the Charbonnier L1 term) and, in
 // e, the data cost of the row.
-FI float gen_residual(const AS4 ScgState &st, const AS4 Proj &P, i64 r, float ax, double &e) {
-    const float rr = ax - glb((const float *)P.y)[r] * st.wt.y_scale;
+FI float gen_residual(const AS4 ScgState &st, float y, float ax, double &e) {
+    const float rr = ax - y * st.wt.y_scale;
     if (st.wt.data_p == 2) {
         e = (double)rr * (double)rr;
         return 2.f * rr;
@@ -503,6 +590,30 @@ FI float gen_residual(const AS4 ScgState &st, const AS4 Proj &P, i64 r, float ax
     e = (double)ph;
     return ps;
 }
+
+// Residuals for mf_adjoint: of the trial point (from A x + alpha A p as they
+// are read), and as stored.
+struct TrialRes {
+    const AS4 ScgState &st;
+    const AS1 float *y, *ax, *ap;
+    float af;
+    struct Raw {
+        float y, ax, ap;
+    };
+    FI Raw load(i64 row, unsigned j) const {
+        return {*at32(y + row, j), *at32(ax + row, j), *at32(ap + row, j)};
+    }
+    FI float value(const Raw &v) const {
+        double e;
+        return gen_residual(st, v.y, fmaf(af, v.ap, v.ax), e);
+    }
+};
+struct StoredRes {
+    const AS1 float *r;
+    using Raw = float;
+    FI Raw load(i64 row, unsigned j) const { return *at32(r + row, j); }
+    FI float value(Raw v) const { return v; }
+};
 
 // BTV prior at HR pixel (ui, vi) of x_t, given at offsets (dy, dx) from the
 // pixel by xo(dy, dx): adds its gradient to g and returns its cost over the
@@ -651,13 +762,13 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_lr(const Proj *projs, co
         {
             for (int q = 0; q < kMfLRG && mf_lr_tile(op, itm.ty, q, k, ti, tj); ++q) {
                 float ax[kMfCPT];
-                mf_forward<S>(op, k, ti, tj, [&](i64 b, unsigned c) { return at32(x + b, c); }, zs, i,
+                mf_forward<S>(op, k, ti, tj, [&](i64 b, unsigned c) { return *at32(x + b, c); }, zs, i,
                               j, ax);
 #pragma unroll
                 for (int c = 0; c < kMfCPT; ++c)
                     if (i + c < h && j < w) {
                         const i64 row = ((i64)k * h + i + c) * w + j;
-                        glbw(P.res)[row] = gen_residual(st, P, row, ax[c], er);
+                        glbw(P.res)[row] = gen_residual(st, glb((const float *)P.y)[row], ax[c], er);
                         e += er;
                         glbw(P.ax[xc])[row] = ax[c];
                         glbw(P.ap[xc])[row] = 0.f;
@@ -670,7 +781,7 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_lr(const Proj *projs, co
         // mode 0 reads x alone: p is not yet initialised there
         if (r < rows) {
             glbw(P.res)[r] = gen_residual(
-                st, P, r,
+                st, glb((const float *)P.y)[r],
                 ell_row(glb(op.a_col), glb(op.a_val), op.a_w, rows, r,
                         [&](i64 c) { return mode == 1 ? fmaf(af, p[c], x[c]) : x[c]; }),
                 er);
@@ -688,19 +799,23 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_lr(const Proj *projs, co
 // from A x + alpha A p as its window is staged (LR pixels shared by
 // neighbouring tiles by each of them), so the trial is this one launch; the
 // data cost goes by the LR items, each of which counts kGenRows kMfCPT rows.
-// Bound by instructions and LDS reads (the prior's eight pairs, the 9
-// candidates of each pixel and frame); back-projected one position per thread
-// it took 48 us on a 1024^2 image (s = 2, 4 frames), after a 7 us launch that
-// only formed the residual; by cells on the matrix cores, without that
-// launch, 48 us in all.  Scale 3, 1020 x 1023, 3 frames, mode 0: 81 -> 58 us.
+// Bound by instructions (the prior's eight pairs, the 9 candidates of each
+// pixel and frame) with waits at three barriers a frame: the matrix-core cells,
+// a frame's residuals loaded under the frame before, the geometry of all
+// frames at once.  1024^2 image, s = 2, 4 frames: 48 us after a 7 us launch
+// that only formed the residual -> 41 us in all; 1020 x 1023, s = 3, 3 frames,
+// mode 0: 81 -> 56 us.
 template <int S>
 __global__ void __launch_bounds__(kGenRows) k_gen_trial_hr(const Proj *projs, const Item *items,
                                                            const int *n_items, double *partials,
                                                            int mode) {
     __shared__ double red[kNV * (kGenRows / 64)];
     __shared__ float lds[kMfWin + kMfQP * kMfQP];
-    const int it = blockIdx.x;
-    if (it >= *cst(n_items)) return;
+    // from the end of the list, where a solve's HR tiles are: they take 20 us
+    // and its LR items 4, which fill in behind them (LR items first: 44.4 us
+    // on a 1024^2 image, HR tiles first: 40.6)
+    const int it = *cst(n_items) - 1 - (int)blockIdx.x;
+    if (it < 0) return;
     const AS4 Item &itm = cst(items)[it];
     const AS4 Proj &P = cst(projs)[itm.proj];
     const AS4 OpDev &op = *cst(P.op);
@@ -725,7 +840,7 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_hr(const Proj *projs, co
             const i64 r = ((i64)itm.ty * kMfCPT + c) * kGenRows + threadIdx.x;
             double e;
             if (r < (i64)op.K * h * w) {
-                (void)gen_residual(st, P, r, fmaf(af, ap[r], ax[r]), e);
+                (void)gen_residual(st, glb((const float *)P.y)[r], fmaf(af, ap[r], ax[r]), e);
                 ed += e;
             }
         }
@@ -751,11 +866,11 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_hr(const Proj *projs, co
         const int tu = itm.ty / ntv, tv = itm.ty - tu * ntv;
         float acc[4] = {0.f, 0.f, 0.f, 0.f};
         {
-            mf_adjoint<S>(op, tu, tv, [&](int k, int i, int j) {
-                const i64 r = ((i64)k * h + i) * w + j;
-                double e;
-                return mode == 1 ? gen_residual(st, P, r, fmaf(af, ap[r], ax[r]), e) : res[r];
-            }, lds, acc);
+            if (mode == 1)
+                mf_adjoint<S>(op, tu, tv, TrialRes{st, glb((const float *)P.y), ax, ap, af}, lds,
+                              acc);
+            else
+                mf_adjoint<S>(op, tu, tv, StoredRes{res}, lds, acc);
         }
         // x_t on the tile and two pixels around it, for the prior's pairs,
         // and g_k, p of the thread's pixels: every load before its use
@@ -910,7 +1025,7 @@ FI void gen_upd_lr_mf(const AS4 Item &itm, const AS4 Proj &P, const AS4 ScgState
         for (int q = 0; q < kMfLRG && mf_lr_tile(op, itm.ty, q, k, ti, tj); ++q) {
             float ap[kMfCPT];
             mf_forward<S>(op, k, ti, tj, [&](i64 b, unsigned c) {
-                return fmaf(bf, at32(p + b, c), -at32(gt + b, c));
+                return fmaf(bf, *at32(p + b, c), -*at32(gt + b, c));
             }, zs, i, j, ap);
 #pragma unroll
             for (int c = 0; c < kMfCPT; ++c)
@@ -1035,7 +1150,7 @@ __global__ void __launch_bounds__(kGenRows) k_mf_forward(const OpDev *opp, const
     {
         for (int q = 0; q < kMfLRG && mf_lr_tile(op, blockIdx.x, q, k, ti, tj); ++q) {
             float ax[kMfCPT];
-            mf_forward<S>(op, k, ti, tj, [&](i64 b, unsigned c) { return at32(xg + b, c); }, zs, i, j,
+            mf_forward<S>(op, k, ti, tj, [&](i64 b, unsigned c) { return *at32(xg + b, c); }, zs, i, j,
                           ax);
 #pragma unroll
             for (int c = 0; c < kMfCPT; ++c)
@@ -1055,9 +1170,7 @@ __global__ void __launch_bounds__(kGenRows) k_mf_adjoint(const OpDev *opp, const
     const int tu = blockIdx.x / ntv, tv = blockIdx.x - tu * ntv;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     {
-        mf_adjoint<S>(op, tu, tv,
-                            [&](int k, int i, int j) { return rg[((i64)k * h + i) * w + j]; }, lds,
-                            acc);
+        mf_adjoint<S>(op, tu, tv, StoredRes{rg}, lds, acc);
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {

@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
 # H, W, s, K, P: LR tiles are 8 x 64 pixels, HR tiles 16 x 64
 EDGES = [(2, 2, 2, 1, 3), (16, 128, 2, 2, 5), (18, 130, 2, 3, 7), (14, 126, 2, 2, 3),
          (34, 66, 2, 2, 11), (48, 195, 3, 2, 3), (51, 63, 3, 3, 5), (27, 198, 3, 2, 9),
-         (36, 260, 4, 2, 5), (32, 60, 4, 2, 15), (17, 65, 1, 2, 3), (15, 63, 1, 3, 7)]
+         (36, 260, 4, 2, 5), (32, 60, 4, 2, 15), (17, 65, 1, 2, 3), (15, 63, 1, 3, 7),
+         (20, 66, 2, 16, 5)]
 
 
 @pytest.mark.parametrize("H,W,s,K,P", EDGES)
