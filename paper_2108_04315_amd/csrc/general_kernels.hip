@@ -803,7 +803,7 @@ __global__ void __launch_bounds__(kGenRows) k_gen_trial_lr(const Proj *projs, co
 // pixel and frame) with waits at three barriers a frame: the matrix-core cells,
 // a frame's residuals loaded under the frame before, the geometry of all
 // frames at once.  1024^2 image, s = 2, 4 frames: 48 us after a 7 us launch
-// that only formed the residual -> 41 us in all; 1020 x 1023, s = 3, 3 frames,
+// that only formed the residual -> 41 us in all; 633 x 909, s = 3, 9 frames,
 // mode 0: 81 -> 56 us.
 template <int S>
 __global__ void __launch_bounds__(kGenRows) k_gen_trial_hr(const Proj *projs, const Item *items,
