@@ -79,8 +79,15 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
                {refs, pl.refs.data(), ns * sizeof(SolveRef)},
                {halos, pl.halos.data(), nh * sizeof(HaloCopy)},
                {states, pl.states.data(), ns * sizeof(ScgState)}};
+    // A call captured into the caller's graph writes these arrays whenever that
+    // graph is replayed: from then on nothing is known about what they hold.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+    captured |= cap != hipStreamCaptureStatusNone;
     constexpr int kStates = 6;
     if (states_dirty) held[kStates].p = nullptr;
+    if (captured)
+        for (auto &hd : held) hd.p = nullptr;
     PutArgs put;
     put.n = 0;
     size_t at = 0;   // bytes in put

@@ -272,6 +272,7 @@ struct PlanDev {
     };
     Held held[7];
     bool states_dirty = true;
+    bool captured = false;   // some call was captured by the caller: every call uploads
     ~PlanDev() {
         if (exec) (void)hipGraphExecDestroy(exec);
     }
