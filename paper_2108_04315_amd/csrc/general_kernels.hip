@@ -350,6 +350,10 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
             raw[q] = res.load(((i64)k * h + i) * w, jc);
         }
     };
+    // taps an LR pixel, per axis, of the product by cells below; 0: positions
+    // one by one (scale 1, where a cell is a position and the taps are many,
+    // PSFs of more than 5 taps an LR pixel, and of one)
+    const int ntc = S > 1 && NT >= 2 && NT <= 5 ? NT : 0;
     Win nw = window(0);
     load(0, nw);
     for (int k = 0; k < op.K; ++k) {
@@ -367,12 +371,12 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         const int i0 = n.i0, j0 = n.j0, NI = n.NI, NJ = n.NJ;
         float *rsm = lds, *wt = lds + NI * NJ;
         const float inj = 1.f / (float)NJ, irv = 1.f / (float)RV;
-        // the back-projection window: whole cells where those fit the LDS (no
-        // bounds per position but the grid's), else [ua, ub] x [va, vb];
-        // its origin and row stride
+        // the back-projection window: whole cells where cells() forms it and
+        // those fit the LDS (no bounds per position but the grid's), else
+        // [ua, ub] x [va, vb]; its origin and row stride
         const int uc = S * (i0 + NT - 1) - R, vc = S * (j0 + NT - 1) - R;
         const int RUC = S * (NI - NT + 1), RVC = S * (NJ - NT + 1);
-        const bool whole = S > 1 && NT <= 5 && NI * NJ + RUC * RVC <= kMfWin;
+        const bool whole = ntc > 0 && NI * NJ + RUC * RVC <= kMfWin;
         const int uw = whole ? uc : ua, vw = whole ? vc : va, RW = whole ? RVC : RV;
         if (n.rows) {
             const bool in_j = j0 + lane >= 0 && j0 + lane < w;
@@ -398,8 +402,8 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         // fused multiply-adds in the taps' order, as one thread would sum
         // them).  A lane holds its cell's residuals and, of the taps, those of
         // phase lane % 4 of each block.
-        auto cells = [&](auto ntc) {
-            constexpr int NTC = decltype(ntc)::value, NP = S * S, G = (NP + 3) / 4;
+        auto cells = [&](auto nt) {
+            constexpr int NTC = decltype(nt)::value, NP = S * S, G = (NP + 3) / 4;
             const AS1 float *cp = glb(op.gkp) + (i64)k * NP * NTC * NTC;
             const int m = threadIdx.x & 3;
             // blocks of phases taken together: as many as hold their taps in
@@ -458,8 +462,7 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
                 }
             }
         };
-        // positions one by one (scale 1, where a cell is a position and the
-        // taps are many, and PSFs of more than 5 taps an LR pixel)
+        // positions one by one, over [ua, ub] x [va, vb]
         auto positions = [&]() {
             const AS1 float *cp = glb(op.gkp) + (i64)k * QP * QP;
             for (int e = threadIdx.x; e < QP * QP; e += kGenRows) cpl[e] = cp[e];
@@ -483,8 +486,7 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
                 wt[e] = sum;
             }
         };
-        const int nt = S == 1 ? 0 : NT;
-        switch (nt) {   // uniform
+        switch (ntc) {   // uniform
         case 2: cells(std::integral_constant<int, 2>{}); break;
         case 3: cells(std::integral_constant<int, 3>{}); break;
         case 4: cells(std::integral_constant<int, 4>{}); break;
