@@ -41,8 +41,10 @@ FI const AS1 T *glb(const T *p) { return (const AS1 T *)p; }
 template <class T>
 FI AS1 T *glbw(T *p) { return (AS1 T *)p; }
 
-// p + i, i unsigned and below 2^30 elements: from a uniform p the access takes
-// a 32-bit lane offset instead of a 64-bit address.
+// p + i, i unsigned and below kAt32Elems (i sizeof(T) in 32 bits for the largest
+// T, float): from a uniform p the access takes a 32-bit lane offset instead of
+// a 64-bit address.
+constexpr i64 kAt32Elems = 1LL << 30;
 template <class T>
 FI const AS1 T *at32(const AS1 T *p, unsigned i) {
     return (const AS1 T *)((const AS1 char *)p + i * (unsigned)sizeof(T));

@@ -164,7 +164,9 @@ FI void mf_forward(const AS4 OpDev &op, int k, int ti, int tj, V vec, float *zs,
     const int nz = ZR * ZC;
     // the window's extent under the warp (affine: at its corners); where the
     // window and every corner of its samples lie on the grid, the samples need
-    // no bounds, and their addresses are 32-bit offsets from the first
+    // no bounds, and their addresses are 32-bit offsets from the first where
+    // the rows they span hold few enough elements (an enlarging warp of a very
+    // wide image spans more)
     double rmin = 1e300, rmax = -1e300, cmin = 1e300, cmax = -1e300;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -177,7 +179,8 @@ FI void mf_forward(const AS4 OpDev &op, int k, int ti, int tj, V vec, float *zs,
     }
     constexpr double kTol = 1e-6;   // (above the corners' own rounding)
     if (u0 >= 0 && v0 >= 0 && u0 + ZR <= H && v0 + ZC <= W && rmin >= kTol && cmin >= kTol &&
-        rmax <= H - 1 - kTol && cmax <= W - 1 - kTol) {
+        rmax <= H - 1 - kTol && cmax <= W - 1 - kTol &&
+        (rmax - rmin + 3.0) * W < kAt32Elems) {
         const int rb = uni((int)rmin), cb = uni((int)cmin);
         const i64 base = (i64)rb * W + cb;
         for (int e0 = threadIdx.x; e0 < nz; e0 += kMfSU * kGenRows) {
