@@ -42,6 +42,14 @@
  * given HIP stream (a hipStream_t passed as void*, NULL = default stream) unless
  * a function says it synchronises.  Calls that share an op must not overlap in
  * time on different streams (the op's workspace is shared).
+ *
+ * Capture.  misr_forward, misr_adjoint, misr_interpolate, misr_upsample,
+ * misr_cost_grad and misr_cost_grad_noalloc may be captured into a graph of the
+ * caller's; a replay does what the captured call would have done, whatever has
+ * run on the op since (workspace the graph uses is kept until the op is
+ * destroyed), and counts as a call on the op.  The op and the call's buffers
+ * must outlive the graph.  A first call may allocate workspace, which some
+ * capture modes forbid: call once before.
  */
 #ifndef MISR_H
 #define MISR_H

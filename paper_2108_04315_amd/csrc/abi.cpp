@@ -34,6 +34,12 @@ misr_status hip_fail(hipError_t e, const char *what) {
 
 size_t dtype_size(misr_dtype dt) { return dt == MISR_F32 ? 4 : 2; }
 
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+    return cap != hipStreamCaptureStatusNone;
+}
+
 hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
     hipError_t e;
     const size_t np = pl.projs.size(), ni = pl.items.size(), nu = pl.items_u.size(),
@@ -81,9 +87,14 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
                {states, pl.states.data(), ns * sizeof(ScgState)}};
     // A call captured into the caller's graph writes these arrays whenever that
     // graph is replayed: from then on nothing is known about what they hold.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
-    captured |= cap != hipStreamCaptureStatusNone;
+    // The graph goes on using these blocks, and its copies read their source
+    // when they run: both stay as they are now (Kept).
+    const bool cap = kept && capturing(stream);
+    captured |= cap;
+    if (cap)
+        for (DevMem *m : {&projs, &items, &items_u, &counts, &states, &partials, &partials_u,
+                          &traces, &refs, &halos})
+            m->keep(*kept);
     constexpr int kStates = 6;
     if (states_dirty) held[kStates].p = nullptr;
     if (captured)
@@ -103,7 +114,8 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
             std::memcpy((unsigned char *)put.w + at, u.h, u.n);
             at += u.n;
         } else {
-            e = hipMemcpyAsync(u.d.p, u.h, u.n, hipMemcpyHostToDevice, stream);
+            const void *src = cap ? kept->copy(u.h, u.n) : u.h;
+            e = hipMemcpyAsync(u.d.p, src, u.n, hipMemcpyHostToDevice, stream);
             if (e != hipSuccess) return e;
         }
         hd.b.assign((const unsigned char *)u.h, (const unsigned char *)u.h + u.n);
@@ -699,6 +711,7 @@ extern "C" misr_status misr_op_create(misr_ctx *ctx, const misr_geometry *g, mis
     MISR_HIP(set_device(ctx->dev));
     auto op = std::make_unique<misr_op>();
     op->ctx = ctx;
+    op->pdev.kept = &op->kept;
     op->H = g->hr_h;
     op->W = g->hr_w;
     op->s = g->scale;
@@ -1424,6 +1437,10 @@ extern "C" misr_status misr_cost_grad(const misr_op *cop, const misr_params *prm
     pl.steps = false;
     PlanDev &pd = op->pdev;
     hipStream_t s = (hipStream_t)stream;
+    if (capturing(s)) {
+        op->bufs.keep(op->kept);
+        if (prm->tile_lr > 0) op->tiles.keep(op->kept);
+    }
     MISR_HIP(pd.upload(pl, 0, s));
     const Launcher Lr{pl, pd, s};
     const int np = (int)pl.projs.size();

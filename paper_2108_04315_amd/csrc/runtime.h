@@ -5,8 +5,10 @@
 
 #include <atomic>
 #include <iterator>
+#include <list>
 #include <map>
 #include <cstdarg>
+#include <cstring>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -130,16 +132,38 @@ struct MemPool {
     ~MemPool() { trim(0); }
 };
 
+// What calls recorded into a caller's graph read and write at every replay,
+// however the operator's own arrays have changed since: the device blocks they
+// were recorded with, and the bytes that recorded uploads copy from.
+struct Kept {
+    std::vector<void *> dev;
+    std::list<std::vector<unsigned char>> host;
+    Kept() = default;
+    Kept(const Kept &) = delete;
+    Kept &operator=(const Kept &) = delete;
+    ~Kept() {
+        for (void *p : dev) (void)hipFree(p);
+    }
+    // a copy of n bytes that stays (one for calls that upload the same)
+    const void *copy(const void *p, size_t n) {
+        for (auto &b : host)
+            if (b.size() == n && !std::memcmp(b.data(), p, n)) return b.data();
+        host.emplace_back((const unsigned char *)p, (const unsigned char *)p + n);
+        return host.back().data();
+    }
+};
+
 struct DevMem {
     void *p = nullptr;
     size_t n = 0;
     MemPool *pool = nullptr;   // blocks come from / go back to this cache if set
+    bool kept = false;         // the block belongs to a Kept: used here, not freed here
     DevMem() = default;
     DevMem(const DevMem &) = delete;
     DevMem &operator=(const DevMem &) = delete;
     ~DevMem() { release(); }
     void release() {
-        if (p) {
+        if (p && !kept) {
             if (pool)
                 pool->put(p, n);
             else
@@ -147,6 +171,13 @@ struct DevMem {
         }
         p = nullptr;
         n = 0;
+        kept = false;
+    }
+    // the block outlives its use here (a recorded call has its address)
+    void keep(Kept &k) {
+        if (!p || kept) return;
+        k.dev.push_back(p);
+        kept = true;
     }
     hipError_t ensure(size_t bytes) {
         if (bytes <= n && p) return hipSuccess;
@@ -239,6 +270,9 @@ struct SolveBufs {
         if ((e = g0.ensure(n * 4)) != hipSuccess) return e;
         return g1.ensure(n * 4);
     }
+    void keep(Kept &k) {
+        for (DevMem *m : {&x1, &p0, &p1, &g0, &g1, &x0w, &res}) m->keep(k);
+    }
     size_t bytes() const { return x1.n + p0.n + p1.n + g0.n + g1.n + x0w.n + res.n; }
     // an untiled solve with parameters p over n HR pixels
     hipError_t ensure_view(long long n, const misr_params &p) {
@@ -255,6 +289,10 @@ struct TileSet {
     MemPool *pool = nullptr;   // for the tile buffers, if set
     std::vector<std::unique_ptr<SolveBufs>> bufs;
     std::vector<std::unique_ptr<DevMem>> x0;
+    void keep(Kept &k) {
+        for (auto &b : bufs) b->keep(k);
+        for (auto &m : x0) m->keep(k);
+    }
 };
 
 // Device mirrors of a Plan plus an instantiated graph of the whole solve.
@@ -273,6 +311,7 @@ struct PlanDev {
     Held held[7];
     bool states_dirty = true;
     bool captured = false;   // some call was captured by the caller: every call uploads
+    Kept *kept = nullptr;    // of the operator whose calls may be captured
     ~PlanDev() {
         if (exec) (void)hipGraphExecDestroy(exec);
     }
@@ -312,6 +351,7 @@ struct misr_op {
     // final SCG state of the last misr_scg_solve (read by misr_scg_status)
     misr::DevMem last_state;
     bool have_last = false;
+    misr::Kept kept;                   // of calls captured by the caller
     // cached workspace of the single-image entry points
     misr::SolveBufs bufs;
     misr::TileSet tiles;
@@ -321,6 +361,8 @@ struct misr_op {
 
 namespace misr {
 
+// Whether work enqueued on the stream is recorded into a caller's graph.
+bool capturing(hipStream_t stream);
 // SCG state of a new solve from its parameters (N = HR pixels).
 void init_state(ScgState &s, const misr_params &p, long long N);
 // Whether an untuned operator of this geometry runs the narrow tiles.
