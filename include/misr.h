@@ -49,7 +49,9 @@
  * run on the op since (workspace the graph uses is kept until the op is
  * destroyed), and counts as a call on the op.  The op and the call's buffers
  * must outlive the graph.  A first call may allocate workspace, which some
- * capture modes forbid: call once before.
+ * capture modes forbid: call once before.  Solves (misr_scg_solve and
+ * misr_scg_solve_batch) are graphs of the library's own and return MISR_E_HIP on
+ * a stream that is being captured, leaving the capture as it is.
  */
 #ifndef MISR_H
 #define MISR_H

@@ -1237,6 +1237,15 @@ static hipError_t enqueue_solve(const Plan &pl, PlanDev &pd, int n_iter, ScgStat
                      : launch_finalize(s, pd.projs.as<Proj>(), np, pl.vt);
 }
 
+// A solve is a graph of its own, which HIP launches at once also where the
+// stream is being captured: it would run now, on whatever the operator's
+// arrays hold, and not when the caller's graph does.
+static misr_status check_not_capturing(hipStream_t s) {
+    return capturing(s) ? set_error(MISR_E_HIP, "a solve cannot be captured: the stream is "
+                                    "recording a graph")
+                        : MISR_OK;
+}
+
 // Runs a plan; the solve is captured into a graph (on the context's library
 // stream) once per plan shape and replayed.  A single solve replays on the
 // caller's stream: its workspace is the operator's, whose calls the caller
@@ -1460,6 +1469,7 @@ extern "C" misr_status misr_scg_solve(const misr_op *cop, const misr_params *prm
     if (st != MISR_OK) return st;
     if ((st = check_general(op, *prm)) != MISR_OK) return st;
     if ((st = check_tiling(op, *prm)) != MISR_OK) return st;
+    if ((st = check_not_capturing((hipStream_t)stream)) != MISR_OK) return st;
     std::lock_guard<std::mutex> lk(op->mu);
     std::lock_guard<std::mutex> lc(op->ctx->mu);
     MISR_HIP(set_device(op->ctx->dev));
@@ -1543,6 +1553,8 @@ extern "C" misr_status misr_scg_solve_batch(int n, const misr_op *const *ops,
         if (ctx && ops[i]->ctx != ctx) return set_error(MISR_E_INVAL, "ops span contexts");
         ctx = ops[i]->ctx;
     }
+    const misr_status cap = check_not_capturing((hipStream_t)stream);
+    if (cap != MISR_OK) return cap;
     std::lock_guard<std::mutex> lk(g_batch_mu);
     std::lock_guard<std::mutex> lc(ctx->mu);
     MISR_HIP(set_device(ctx->dev));
