@@ -281,11 +281,15 @@ extern "C" misr_status misr_ctx_create(int dev, misr_ctx **out) {
     return MISR_OK;
 }
 
+// Gives back what batches on the context keep (with BatchCache below).
+static void drop_batch(const misr_ctx *c);
+
 extern "C" misr_status misr_ctx_destroy(misr_ctx *c) {
     if (!c) return set_error(MISR_E_INVAL, "ctx is NULL");
     if (c->users.load() > 0)
         return set_error(MISR_E_BUSY, "%d ops/servers still use this context", c->users.load());
     (void)hipStreamSynchronize(c->stream);
+    drop_batch(c);
     (void)hipEventDestroy(c->ev_in);
     (void)hipEventDestroy(c->ev_out);
     (void)hipStreamDestroy(c->stream);
@@ -1533,6 +1537,14 @@ size_t batch_bytes(const misr_op *op, const misr_params &p) {
     return b;
 }
 }  // namespace
+
+// (a later context may have this one's address, and another device)
+static void drop_batch(const misr_ctx *c) {
+    std::lock_guard<std::mutex> lk(g_batch_mu);
+    if (!g_batch || g_batch->ctx != c) return;
+    delete g_batch;
+    g_batch = nullptr;
+}
 
 extern "C" misr_status misr_scg_solve_batch(int n, const misr_op *const *ops,
                                             const misr_params *prm, const void *const *y,
