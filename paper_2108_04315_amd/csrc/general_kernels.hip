@@ -112,28 +112,36 @@ FI bool mf_lr_tile(const AS4 OpDev &op, int t, int q, int &k, int &ti, int &tj) 
 FI int mf_div(int e, float inv) { return (int)(((float)e + 0.5f) * inv); }
 
 // The two LR pixels' Q x Q windows times the kernel ck: window row a is row a
-// of the first pixel and row a - S of the second.  The usual kernel sizes
-// (QC: PSFs of 5 and 7 taps) are unrolled whole, so that their weights and
-// window reads are in flight together.
-template <int S, int QC>
-FI void mf_conv(const float *zb, int ZC, const AS4 float *ck, int Q, float (&acc)[kMfCPT]) {
-    if constexpr (QC > 0) {
+// of the first pixel and row a - S of the second.  PSFs of up to 7 taps are
+// unrolled whole, larger ones by rows, so that a row's weights and window reads
+// are in flight together (with Q a variable and four columns at a time, the
+// forward of 2 frames of 330 x 410 at s = 3 with 15-tap PSFs took 48 us, now 24).
+template <int S, int Q>
+FI void mf_conv(const float *zb, int ZC, const AS4 float *ck, float (&acc)[kMfCPT]) {
+    if constexpr (Q <= S + 6) {
 #pragma unroll
-        for (int a = 0; a < QC + S; ++a)
-#pragma unroll
-            for (int b = 0; b < QC; ++b) {
-                const float z = zb[a * ZC + b];
-                if (a < QC) acc[0] = fmaf(ck[a * QC + b], z, acc[0]);
-                if (a >= S) acc[1] = fmaf(ck[(a - S) * QC + b], z, acc[1]);
-            }
-    } else {
         for (int a = 0; a < Q + S; ++a)
-#pragma unroll 4
+#pragma unroll
             for (int b = 0; b < Q; ++b) {
                 const float z = zb[a * ZC + b];
                 if (a < Q) acc[0] = fmaf(ck[a * Q + b], z, acc[0]);
                 if (a >= S) acc[1] = fmaf(ck[(a - S) * Q + b], z, acc[1]);
             }
+    } else {
+#pragma unroll 1
+        for (int a = 0; a < Q + S; ++a) {
+            float z[Q];
+#pragma unroll
+            for (int b = 0; b < Q; ++b) z[b] = zb[a * ZC + b];
+            if (a < Q) {
+#pragma unroll
+                for (int b = 0; b < Q; ++b) acc[0] = fmaf(ck[a * Q + b], z[b], acc[0]);
+            }
+            if (a >= S) {
+#pragma unroll
+                for (int b = 0; b < Q; ++b) acc[1] = fmaf(ck[(a - S) * Q + b], z[b], acc[1]);
+            }
+        }
     }
 }
 
@@ -235,11 +243,18 @@ FI void mf_forward(const AS4 OpDev &op, int k, int ti, int tj, V vec, float *zs,
     const float *zb = zs + S * il * ZC + S * jl;
     float acc[kMfCPT] = {0.f, 0.f};
     if (Q == S + 6)
-        mf_conv<S, S + 6>(zb, ZC, ck, Q, acc);
+        mf_conv<S, S + 6>(zb, ZC, ck, acc);
     else if (Q == S + 4)
-        mf_conv<S, S + 4>(zb, ZC, ck, Q, acc);
+        mf_conv<S, S + 4>(zb, ZC, ck, acc);
     else
-        mf_conv<S, 0>(zb, ZC, ck, Q, acc);
+        switch (op.P) {   // uniform; odd, at most 15 (misr_geometry_check)
+        case 1: mf_conv<S, S>(zb, ZC, ck, acc); break;
+        case 3: mf_conv<S, S + 2>(zb, ZC, ck, acc); break;
+        case 9: mf_conv<S, S + 8>(zb, ZC, ck, acc); break;
+        case 11: mf_conv<S, S + 10>(zb, ZC, ck, acc); break;
+        case 13: mf_conv<S, S + 12>(zb, ZC, ck, acc); break;
+        default: mf_conv<S, S + 14>(zb, ZC, ck, acc); break;
+        }
     __syncthreads();
     i = i0 + il;
     j = j0 + jl;
