@@ -292,7 +292,7 @@ template <int S, class Rf>
 FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, float (&acc)[4]) {
     const int H = op.H, W = op.W, Q = op.Q, R = (op.P - 1) / 2;
     const int h = H / S, w = W / S;
-    const int NT = (Q + S - 1) / S, QP = S * NT;
+    const int NT = (Q + S - 1) / S;
     const int U0 = tu * kMfTU, V0 = tv * kMfTV;
     const int U1 = min(U0 + kMfTU, H) - 1, V1 = min(V0 + kMfTV, W) - 1;
     const int row = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -369,9 +369,11 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         }
     };
     // taps an LR pixel, per axis, of the product by cells below; 0: positions
-    // one by one (scale 1, where a cell is a position and the taps are many,
-    // PSFs of more than 5 taps an LR pixel, and of one)
-    const int ntc = S > 1 && NT >= 2 && NT <= 5 ? NT : 0;
+    // one by one, at scale 1 (where a cell is a position and the taps are many),
+    // for one tap, more than 5, and 5 at scale 4 (16 phases of 25 taps are four
+    // loads of taps for about 100 cells a tile: adjoint of 4 frames of 330 x 410
+    // with 15-tap PSFs 75.7 us by cells, 66.5 by positions)
+    const int ntc = S > 1 && NT >= 2 && NT <= (S == 4 ? 4 : 5) ? NT : 0;
     Win nw = window(0);
     load(0, nw);
     for (int k = 0; k < op.K; ++k) {
@@ -388,7 +390,7 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         const int RU = ub - ua + 1, RV = vb - va + 1;
         const int i0 = n.i0, j0 = n.j0, NI = n.NI, NJ = n.NJ;
         float *rsm = lds, *wt = lds + NI * NJ;
-        const float inj = 1.f / (float)NJ, irv = 1.f / (float)RV;
+        const float inj = 1.f / (float)NJ;
         // the back-projection window: whole cells where cells() forms it and
         // those fit the LDS (no bounds per position but the grid's), else
         // [ua, ub] x [va, vb]; its origin and row stride
@@ -480,10 +482,24 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
                 }
             }
         };
-        // positions one by one, over [ua, ub] x [va, vb]
-        auto positions = [&]() {
-            const AS1 float *cp = glb(op.gkp) + (i64)k * QP * QP;
-            for (int e = threadIdx.x; e < QP * QP; e += kGenRows) cpl[e] = cp[e];
+        // positions one by one, over [ua, ub] x [va, vb]; the taps' count is
+        // known to the compiler where it is small (0: NT).  The phases' taps lie
+        // an odd number of words apart: neighbouring positions are of different
+        // phases, and an even square put them in the same bank.
+        auto positions = [&](auto nt) {
+            constexpr int NTC = decltype(nt)::value, UT = S == 1 ? 6 : 1;
+            int n1 = NTC > 0 ? NTC : NT;
+            if (NTC == 0) asm volatile("" : "+s"(n1));   // (nothing of this is kept across frames)
+            const int n2 = n1 * n1, pst = n2 | 1, nk = S * S * n2;
+            const float irv = 1.f / (float)RV;
+            const AS1 float *cp = glb(op.gkp) + (i64)k * nk;
+            if (S == 1 || pst == n2) {
+                for (int e = threadIdx.x; e < nk; e += kGenRows) cpl[e] = cp[e];
+            } else {
+                const float in2 = 1.f / (float)n2;
+                for (int e = threadIdx.x; e < nk; e += kGenRows)
+                    cpl[e + mf_div(e, in2)] = cp[e];
+            }
             ahead();
             __syncthreads();
             for (int e = threadIdx.x; e < RU * RV; e += kGenRows) {
@@ -492,14 +508,13 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
                 float sum = 0.f;
                 if (u >= 0 && u < H && v >= 0 && v < W) {
                     const int qu = fdiv(u + R, S), qv = fdiv(v + R, S);
-                    const float *cr =
-                        cpl + ((u + R - S * qu) * S + (v + R - S * qv)) * NT * NT;
+                    const float *cr = cpl + ((u + R - S * qu) * S + (v + R - S * qv)) * pst;
                     const float *rr = rsm + (qu - i0) * NJ + (qv - j0);
+#pragma unroll UT
+                    for (int t = 0; t < n1; ++t)
 #pragma unroll 6
-                    for (int t = 0; t < NT; ++t)
-#pragma unroll 6
-                        for (int t2 = 0; t2 < NT; ++t2)
-                            sum = fmaf(cr[t * NT + t2], rr[-t * NJ - t2], sum);
+                        for (int t2 = 0; t2 < n1; ++t2)
+                            sum = fmaf(cr[t * n1 + t2], rr[-t * NJ - t2], sum);
                 }
                 wt[e] = sum;
             }
@@ -508,8 +523,17 @@ FI void mf_adjoint(const AS4 OpDev &op, int tu, int tv, Rf res, float *lds, floa
         case 2: cells(std::integral_constant<int, 2>{}); break;
         case 3: cells(std::integral_constant<int, 3>{}); break;
         case 4: cells(std::integral_constant<int, 4>{}); break;
-        case 5: cells(std::integral_constant<int, 5>{}); break;
-        default: positions(); break;
+        case 5:
+            if constexpr (S < 4) cells(std::integral_constant<int, 5>{});
+            break;
+        default:
+            if (S == 1 && NT == 3)
+                positions(std::integral_constant<int, 3>{});
+            else if ((S == 1 || S == 4) && NT == 5)
+                positions(std::integral_constant<int, 5>{});
+            else
+                positions(std::integral_constant<int, 0>{});
+            break;
         }
         __syncthreads();
         const float m0f = (float)op.gm[k][0], m1f = (float)op.gm[k][1];
