@@ -919,12 +919,21 @@ FI void tile_trial(const AS4 Proj &P, const AS4 ScgState &st, int ty, int tx, in
     const float eps = st.wt.eps;
     double e_reg = 0.0;
     // interior tiles: every pair of the sweep lies inside the image, tile owned
-    // whole; a narrow tile goes by the wide tile it lies in
+    // whole.  A narrow tile's wave goes by the wide tile that its columns lie in:
+    // where the widths do not divide (56 and 24 columns, 80 and 32), a narrow
+    // tile lies across two wide ones, of which the second may be cut by the edge;
+    // at scale 1 so may a wave's columns, which then go by both.
     constexpr int TWW = TV == kNarrow ? Tile<S, L, 0>::TW : T::TW;
     const int vrel = o.v0 - P.ox0, vin = vrel % TWW;
-    const bool inner = o.U0 >= 2 && o.V0 - vin >= 2 && o.U0 + T::TH + 2 <= H &&
-                       o.V0 - vin + TWW + 2 <= W && o.u1 - o.u0 == T::TH &&
-                       o.v0 - vin + TWW <= P.ox1;
+    auto inner_cols = [&](int v) {   // the (wide) tile that holds column v (from ox0)
+        const int a = v - v % TWW;
+        return P.gx0 + P.ox0 + a >= 2 && P.gx0 + P.ox0 + a + TWW + 2 <= W &&
+               P.ox0 + a + TWW <= P.ox1;
+    };
+    const int vw = TV == kNarrow ? vrel + wv0 * T::CV : vrel;
+    const bool inner = o.U0 >= 2 && o.U0 + T::TH + 2 <= H && o.u1 - o.u0 == T::TH &&
+                       inner_cols(vw) &&
+                       (TWW % T::CV == 0 || inner_cols(vw + T::CV - 1));   // (by wave)
     const int tho = o.u1 - o.u0, two = o.v1 - o.v0;
     const int cw0 = (vin + wv0 * T::CV) % (TWW / kNWI);
     if (eps == 0.f)
