@@ -11,7 +11,7 @@ constexpr int kNT = 256;     // threads per workgroup of the image kernels
 constexpr int kNV = 6;       // FP64 partial sums per work item
 constexpr int kMaxK = 16;    // frames per projection
 constexpr int kMaxL = 16;    // band length
-constexpr int kPadRows = 16; // zero weight rows before each frame's table
+constexpr int kPadRows = 1;  // zero weight rows before and after each frame's table
 
 // Shape key of the narrow tile (tile_hr, tile_wr).
 constexpr int kNarrow = 3;
@@ -26,12 +26,10 @@ constexpr int st_y(int code) { return code >> 4; }
 // Operator of one geometry: per frame the two 1-D factors of A_k.
 // Row factor: LR row i reads HR rows s*i + offy[k] + l, l in [0, L), with
 // weight wy[(k*fsy + i)*L + l]; columns likewise with wx / offx / fsx.
-// wy/wx point at row 0 of frame 0; kPadRows zero rows sit before every
-// frame's rows and fsy - h - kPadRows (fsx - w - kPadRows) after them, so
-// that kernels may index outside [0, h): the adjoint passes compute whole
-// tiles, and a last tile past the image edge reads rows up to about a tile
-// extent / s beyond it (band_pad_after).  cwy[k] / cwx[k]: the weights of the
-// LR rows the image edge does not cut, which are all alike: rows
+// wy/wx point at row 0 of frame 0; a zero row sits before and after every
+// frame's rows, and kernels clamp a row index to [-1, h] (columns [-1, w]): the
+// rows of a last tile past the image edge read it.  cwy[k] / cwx[k]: the weights
+// of the LR rows the image edge does not cut, which are all alike: rows
 // [loy[k], hiy[k]) (columns [lox[k], hix[k])) equal them at every HR row
 // (column) inside the image, the others (a few at either edge) do not.
 //

@@ -280,10 +280,8 @@ static size_t op_bytes_estimate(const misr_geometry &g, bool general) {
         return (size_t)(2 * 8 * e * g.n_frames * h * w) + sizeof(OpDev);
     }
     const int Lp = padded_band(g.scale, band_length(&g));
-    int pad_y = 0, pad_x = 0;
-    band_pad_after(g.scale, Lp, pad_y, pad_x);
-    return (size_t)g.n_frames * (size_t)(h + w + 2 * kPadRows + pad_y + pad_x) *
-               (size_t)std::max(Lp, 1) * 4 + sizeof(OpDev);
+    return (size_t)g.n_frames * (size_t)(h + w + 4 * kPadRows) * (size_t)std::max(Lp, 1) * 4 +
+           sizeof(OpDev);
 }
 
 // Device bytes an operator holds.
