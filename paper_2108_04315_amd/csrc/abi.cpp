@@ -73,7 +73,8 @@ hipError_t PlanDev::upload(Plan &pl, int n_iter, hipStream_t stream) {
     // A repeated call on an operator differs in the views (its buffers) and,
     // after a solve, in the states: short arrays, which go with one launch
     // (launch_put).  Seven copies from pageable memory cost a call about 20 us
-    // of host time before.
+    // of host time.  (An operator's first call allocates the arrays and uploads
+    // all of them.)
     struct Up {
         DevMem &d;
         const void *h;

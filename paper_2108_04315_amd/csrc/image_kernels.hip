@@ -412,7 +412,9 @@ __device__ constexpr int kDY[8] = {0, 0, 1, 1, 1, 2, 2, 2};
 // columns before the strip (first column), and the shares whose partner lies
 // past the strip (last one or two columns).  The narrow tile rounds as the
 // wide one does, so that results do not depend on which of them a pixel falls
-// into: cw0 is the strip's first column within the strips of variant 0.
+// into: cw0 is the strip's first column within the strips of variant 0.  (But
+// for a strip of scale 1 across two wide tiles of which the edge cuts one: all
+// of it rounds as at the edge.)
 template <int S, int L, int TV, bool EPS0, bool CHECK>
 FI void btv_sweep(const float *xs, float *gs, const float (&gam)[8], float eps, int U0, int V0,
                   int H, int W, int th_own, int tw_own, int cw0, double &e_reg) {

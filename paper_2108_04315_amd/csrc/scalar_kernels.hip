@@ -90,8 +90,10 @@ __global__ void k_finalize(const Proj *__restrict__ projs, int nproj, int stype)
 }
 
 // ---------------------------------------------------- tiled-solve helpers
-// Halo exchange: each copy moves a rectangle of the trial gradient g[cur^1]
-// from the view that owns it into another view's halo.  A copy between two
+// Halo exchange: each copy moves a rectangle of the gradient g[cur] from the
+// view that owns it into another view's halo.  It runs after the SCG steps that
+// end a trial pass: an accepted trial's gradient is g[cur] by then; after a
+// rejection the copy repeats values that are already there.  A copy between two
 // neighbours is a strip as long as the view (2048 x 16 HR px at 1024^2-LR tiles
 // with a halo of 8) and moves few bytes per launch, so the launch is bound by
 // how many loads are in flight: kHaloPx pixels of a rectangle per workgroup

@@ -741,7 +741,8 @@ void misr_server::run() {
             // passes this cycle: about 3 ms of device time, at most 32, and no
             // further than the earliest completion (two cycles are enqueued
             // ahead of a new request: with 64, and passes of 45 us, a solve of
-            // 1024^2 HR pixels was committed to its end within 5.5 ms)
+            // 1024^2 HR pixels was committed to its end within 5.5 ms; a stream
+            // of mixed sizes and one of LR 512^2 run the same to 1 %)
             double mpx = 0;
             for (SReq *r : run) mpx += r->n * 1e-6;
             int n_ep = (int)(3000.0 / std::max(1e-3, us_per_mpx_pass * mpx));
