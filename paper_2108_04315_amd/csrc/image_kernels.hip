@@ -288,12 +288,28 @@ FI void pass3_ph(const float *rs, float *tt, int U0, int offy, int iF, int jrel,
                 if (ph + S * m < L) a = fmaf(ay.c[ph + S * m], rv[dq - m + NTAP - 1], a);
             dst[c] = a;
         }
+    } else if constexpr (S > 1) {
+        // tap by tap (by rows, as below, a tiled 4096^2 solve at scale 2 took
+        // 28.3 ms instead of 28.05, the adjoint of 9 frames of 1024^2 at scale 3
+        // 62.7 us instead of 62.3)
+#pragma unroll
+        for (int c = 0; c < CU; ++c) {
+            const int dq = (PH + c) / S, ph = (PH + c) % S;
+            float a = 0.f;
+#pragma unroll
+            for (int m = 0; m < NTAP; ++m)
+                if (ph + S * m < L) {
+                    const AS1 float *wb = (const AS1 float *)ay.row(ib + dq - m + NTAP - 1);
+                    a = fmaf(wb[ph + S * m], rv[dq - m + NTAP - 1], a);
+                }
+            dst[c] = a;
+        }
     } else {
         // row by row from the last, the order of the sums above: a row's taps
         // are neighbours in the table, and four rows' loads are in flight
-        // together.  (Output by output, each with its own row per tap, the loads
-        // of scale 1 and band 16 spilled 90 registers of the trial kernel: cost
-        // and gradient of 16 frames of 33 x 20 took 134 us, now 106.)
+        // together.  (Tap by tap, the loads of band 16 spilled 90 registers of the
+        // trial kernel: cost and gradient of 16 frames of 33 x 20 took 134 us, now
+        // 106.)
         constexpr int G = 4;
         float a[CU];
 #pragma unroll
